@@ -63,6 +63,7 @@ struct MpTabs {
   int tile[NUM_TILE_CFGS] = {};
   Tab<ModeProd<T>> t[NUM_TILE_CFGS];
   bool bf3 = false;
+  int mode = MP_PLAIN;
 };
 
 template <typename T>
@@ -81,7 +82,7 @@ template <typename T>
 bool mp_add(MpTabs<T>& m, const ModeProd<T>& a, int tile) {
   for (int i = 0; i < m.n; ++i)
     if (m.tile[i] == tile) {
-      TableArena::add(m.t[i], a, modeprod_items_for(a.M, a.Nc, a.nbatch, tile, m.bf3));
+      TableArena::add(m.t[i], a, modeprod_items_for(a.M, a.Nc, a.nbatch, m.bf3 ? tile : tile_of(tile, a.mode, sizeof(T) == 8), m.bf3));
       return true;
     }
   return false;
@@ -91,7 +92,7 @@ tp3b_status tile_missing() { return fail(TP3B_EDEVICE, "batched: tile shape with
 
 hipError_t mp_launch(const MpTabs<double>& m, hipStream_t s) {
   for (int i = 0; i < m.n; ++i) {
-    hipError_t e = launch_modeprod_grouped<double>(m.t[i].d, m.tile[i], s);
+    hipError_t e = launch_modeprod_grouped<double>(m.t[i].d, m.tile[i], m.mode, s);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
@@ -99,62 +100,47 @@ hipError_t mp_launch(const MpTabs<double>& m, hipStream_t s) {
 hipError_t mp_launch(const MpTabs<float>& m, hipStream_t s) {
   for (int i = 0; i < m.n; ++i) {
     hipError_t e = m.bf3 ? launch_modeprod_bf3_grouped(m.t[i].d, m.tile[i], s)
-                         : launch_modeprod_grouped<float>(m.t[i].d, m.tile[i], s);
+                         : launch_modeprod_grouped<float>(m.t[i].d, m.tile[i], m.mode, s);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
 }
 
-// Mode-product descriptors of the 1D Hamiltonian apply and of the four
-// preconditioner stages (the same products tp3b.cpp launches one by one).
+// The tables of one grouped preconditioner apply: four steps, each as plain and
+// as folded products (an instance has its job in one of the two).
 template <typename T>
-ModeProd<T> h_job(tp3b_op op, int nvec, const T* X, int64_t ldx, T* Y, int64_t ldy,
-                  const double* shifts) {
-  DevOps<T>& d = dev_ops<T>(op);
-  ModeProd<T> a{};
-  a.M = op->n[0];
-  a.Nc = op->n[1];
-  a.rs = op->n[1];
-  a.bstride = 0;
-  a.ldx = ldx;
-  a.ldy = ldy;
-  a.per_vec = 1;
-  a.nbatch = nvec;
-  a.X = X;
-  a.Y = Y;
-  a.L = d.K[0];
-  a.R = d.KT[1];
-  a.V = d.V;
-  a.shifts = shifts;
-  a.epi = EPI_V;
-  a.acc = 0;
-  return a;
+struct PrecTabs {
+  MpTabs<T> mp[2][4];
+  bool use[2] = {false, false};
+};
+
+template <typename T>
+bool prec_alloc(TableArena& ar, const tp3b_op* ops, int count, const TileSet& ts, int cap, bool bf3, PrecTabs<T>& p) {
+  for (int i = 0; i < count; ++i) p.use[prec_folded(ops[i], bf3)] = true;
+  bool ok = true;
+  for (int f = 0; f < 2; ++f)
+    for (int st = 0; st < 4 && p.use[f]; ++st) {
+      ok = ok && mp_alloc(ar, ts, cap, bf3, p.mp[f][st]);
+      if (f) p.mp[f][st].mode = MP_FOLD_L + st;
+    }
+  return ok;
 }
 
-// Stage st of Z = Sx [(Sx^{-1} B Sy^{-T}) / (lx_i + ly_j - sigma)] Sy^T; the
-// intermediate lives in the operator's work buffer (nv <= work_vecs).
 template <typename T>
-ModeProd<T> prec_job(tp3b_op op, int st, int nv, const T* X, int64_t ldx, T* Y, int64_t ldy) {
-  DevOps<T>& d = dev_ops<T>(op);
-  ModeProd<T> a{};
-  a.M = op->n[0];
-  a.Nc = op->n[1];
-  a.rs = op->n[1];
-  a.per_vec = 1;
-  a.nbatch = nv;
-  a.sigma = op->sigma;
-  a.epi = EPI_NONE;
-  const int64_t N = op->N;
-  switch (st) {
-    case 0: a.X = X; a.ldx = ldx; a.Y = d.work; a.ldy = N; a.L = d.Si[0]; break;
-    case 1:
-      a.X = d.work; a.ldx = N; a.Y = Y; a.ldy = ldy; a.R = d.SiT[1];
-      a.epi = EPI_DIV; a.lamL = d.lam[0]; a.lamR = d.lam[1];
-      break;
-    case 2: a.X = Y; a.ldx = ldy; a.Y = d.work; a.ldy = N; a.L = d.S[0]; break;
-    default: a.X = d.work; a.ldx = N; a.Y = Y; a.ldy = ldy; a.R = d.ST[1]; break;
-  }
-  return a;
+bool prec_add(PrecTabs<T>& p, tp3b_op op, bool bf3, int nv, const T* X, int64_t ldx, T* Y, int64_t ldy, int tile) {
+  const bool fold = prec_folded(op, bf3);
+  for (int st = 0; st < 4; ++st)
+    if (!mp_add(p.mp[fold][st], prec_job<T>(op, st, nv, X, ldx, Y, ldy, fold), tile)) return false;
+  return true;
+}
+
+template <typename T>
+hipError_t prec_launch(const PrecTabs<T>& p, hipStream_t s) {
+  hipError_t e = hipSuccess;
+  for (int st = 0; st < 4; ++st)
+    for (int f = 0; f < 2 && e == hipSuccess; ++f)
+      if (p.use[f]) e = mp_launch(p.mp[f][st], s);
+  return e;
 }
 
 tp3b_status check_batch(const tp3b_op* ops, int count, bool need_prec) {
@@ -176,7 +162,7 @@ TableArena* apply_arena() {
   static thread_local std::unique_ptr<TableArena> ar;
   if (!ar) {
     ar.reset(new TableArena());
-    if (ar->init((size_t)8 << 20) != hipSuccess) {
+    if (ar->init((size_t)16 << 20) != hipSuccess) {
       ar.reset();
       return nullptr;
     }
@@ -196,25 +182,20 @@ tp3b_status apply_batched(const tp3b_op* ops, int count, int nvec, const void* c
   const bool f64 = sizeof(T) == 8;
   TileSet ts;
   for (int i = 0; i < count; ++i) ts.add(op_tile(ops[i], f64, bf3, prec ? 1 : 0, nvec));
-  const int nst = prec ? 4 : 1;
-  MpTabs<T> tabs[4];
-  for (int st = 0; st < nst; ++st)
-    if (!mp_alloc(*ar, ts, count, bf3, tabs[st])) return arena_full();
+  MpTabs<T> h;
+  PrecTabs<T> p;
+  if (!(prec ? prec_alloc(*ar, ops, count, ts, count, bf3, p) : mp_alloc(*ar, ts, count, bf3, h)))
+    return arena_full();
   for (int i = 0; i < count; ++i) {
     const T* x = (const T*)X[i];
     T* y = (T*)Y[i];
     const int tile = op_tile(ops[i], f64, bf3, prec ? 1 : 0, nvec);
-    if (prec) {
-      for (int st = 0; st < 4; ++st)
-        if (!mp_add(tabs[st], prec_job<T>(ops[i], st, nvec, x, ldx[i], y, ldy[i]), tile))
-          return tile_missing();
-    } else {
-      if (!mp_add(tabs[0], h_job<T>(ops[i], nvec, x, ldx[i], y, ldy[i], shifts ? shifts[i] : nullptr), tile))
-        return tile_missing();
-    }
+    if (!(prec ? prec_add(p, ops[i], bf3, nvec, x, ldx[i], y, ldy[i], tile)
+               : mp_add(h, h_job<T>(ops[i], nvec, x, ldx[i], y, ldy[i], shifts ? shifts[i] : nullptr), tile)))
+      return tile_missing();
   }
   TP3B_HIP(ar->upload(s));
-  for (int st = 0; st < nst; ++st) TP3B_HIP(mp_launch(tabs[st], s));
+  TP3B_HIP(prec ? prec_launch(p, s) : mp_launch(h, s));
   return TP3B_OK;
 }
 
@@ -349,7 +330,7 @@ class BatchedJdqr {
   // GMRES tables
   struct GmTabs {
     Tab<ConvJob<double, TW>> rhs_conv;
-    MpTabs<TW> prec[4];
+    PrecTabs<TW> prec;
     Tab<DotJob<TW, TW>> proj_dot;
     Tab<GemmJob<TW>> proj_gemm;
     Tab<BdotJob<TW>> nrm;
@@ -462,8 +443,8 @@ tp3b_status BatchedJdqr<TW>::setup() {
   }
   for (int i = 0; i < count_; ++i) in_[i].flags = (int*)FlagsD_.at(i);
   // ---- job-table arenas
-  TP3B_HIP(ar_.init((size_t)32 << 20));
-  TP3B_HIP(gar_.init((size_t)64 << 20));
+  TP3B_HIP(ar_.init((size_t)40 << 20));
+  TP3B_HIP(gar_.init((size_t)80 << 20));
   // ---- tile shapes
   for (int i = 0; i < count_; ++i) {
     Inst& I = in_[i];
@@ -505,19 +486,16 @@ tp3b_status BatchedJdqr<TW>::prec64(const std::vector<int>& list,
                                     const std::vector<double*>& Y, const std::vector<int>& nv) {
   if (list.empty()) return TP3B_OK;
   TP3B_TRY(arena_room());
-  MpTabs<double> t[4];
-  for (int st = 0; st < 4; ++st)
-    if (!mp_alloc(ar_, tsP64_, (int)list.size(), false, t[st])) return arena_full();
+  PrecTabs<double> t;
+  if (!prec_alloc(ar_, ops_, count_, tsP64_, (int)list.size(), false, t)) return arena_full();
   for (size_t e = 0; e < list.size(); ++e) {
     if (nv[e] <= 0) continue;
     const Inst& I = in_[list[e]];
-    for (int st = 0; st < 4; ++st)
-      if (!mp_add(t[st], prec_job<double>(I.op, st, nv[e], X[e], I.N, Y[e], I.N), I.tP64))
-        return tile_missing();
+    if (!prec_add<double>(t, I.op, false, nv[e], X[e], I.N, Y[e], I.N, I.tP64)) return tile_missing();
     stats_.n_apply_prec += nv[e];
   }
   TP3B_HIP(ar_.upload(s_));
-  for (int st = 0; st < 4; ++st) TP3B_HIP(mp_launch(t[st], s_));
+  TP3B_HIP(prec_launch(t, s_));
   return TP3B_OK;
 }
 
@@ -803,7 +781,7 @@ tp3b_status BatchedJdqr<TW>::build_gmres_tables() {
   g.bu2.assign(steps_, Tab<BupdJob<TW>>());
   g.normk.assign(steps_, Tab<NormJob<TW>>());
   bool ok = gar_.alloc(g.rhs_conv, cap);
-  for (int st = 0; st < 4; ++st) ok = ok && mp_alloc(gar_, tsPW_, cap, bf3_, g.prec[st]);
+  ok = ok && prec_alloc(gar_, ops_, count_, tsPW_, cap, bf3_, g.prec);
   ok = ok && gar_.alloc(g.proj_dot, cap) && gar_.alloc(g.proj_gemm, cap) && gar_.alloc(g.nrm, cap) &&
        gar_.alloc(g.norm0, cap);
   for (int kk = 0; kk < steps_; ++kk) {
@@ -827,8 +805,7 @@ tp3b_status BatchedJdqr<TW>::build_gmres_tables() {
     TableArena::add(g.rhs_conv, ConvJob<double, TW>{N, nb, -1.0, I.Rres, N, use_prec_ ? Zt : W, N},
                     rows_items(N, nb));
     if (use_prec_)
-      for (int st = 0; st < 4; ++st)
-        if (!mp_add(g.prec[st], prec_job<TW>(I.op, st, nb, Zt, N, W, N), I.tPW)) return tile_missing();
+      if (!prec_add<TW>(g.prec, I.op, bf3_, nb, Zt, N, W, N, I.tPW)) return tile_missing();
     {
       DotJob<TW, TW> j{};
       j.N = N; j.p = nqt; j.q = nb; j.A = Qtw; j.lda = N; j.B = W; j.ldb = N;
@@ -881,7 +858,7 @@ tp3b_status BatchedJdqr<TW>::launch_gmres() {
   GmTabs& g = gm_;
   TP3B_HIP(launch_convert_grouped(g.rhs_conv.d, s_));
   if (use_prec_)
-    for (int st = 0; st < 4; ++st) TP3B_HIP(mp_launch(g.prec[st], s_));
+    TP3B_HIP(prec_launch(g.prec, s_));
   TP3B_HIP(launch_dot_grouped(g.proj_dot.d, s_));
   TP3B_HIP(launch_gemm_grouped(g.proj_gemm.d, s_));
   TP3B_HIP(launch_bdot_grouped(g.nrm.d, s_));
@@ -889,7 +866,7 @@ tp3b_status BatchedJdqr<TW>::launch_gmres() {
   for (int kk = 0; kk < steps_; ++kk) {
     TP3B_HIP(mp_launch(g.H[kk], s_));
     if (use_prec_)
-      for (int st = 0; st < 4; ++st) TP3B_HIP(mp_launch(g.prec[st], s_));
+      TP3B_HIP(prec_launch(g.prec, s_));
     TP3B_HIP(launch_dot_grouped(g.proj_dot.d, s_));
     TP3B_HIP(launch_gemm_grouped(g.proj_gemm.d, s_));
     TP3B_HIP(launch_bdot_grouped(g.bd1[kk].d, s_));

@@ -23,7 +23,7 @@ struct Mma;
 template <>
 struct Mma<double> {
   typedef d4 acc_t;
-  static __device__ __forceinline__ int row(int lk, int r) { return lk + 4 * r; }
+  static __device__ __forceinline__ constexpr int row(int lk, int r) { return lk + 4 * r; }
   static __device__ __forceinline__ acc_t mma(double a, double b, acc_t c) {
     return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
   }
@@ -31,7 +31,7 @@ struct Mma<double> {
 template <>
 struct Mma<float> {
   typedef f4 acc_t;
-  static __device__ __forceinline__ int row(int lk, int r) { return 4 * lk + r; }
+  static __device__ __forceinline__ constexpr int row(int lk, int r) { return 4 * lk + r; }
   static __device__ __forceinline__ acc_t mma(float a, float b, acc_t c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
   }
@@ -48,194 +48,10 @@ __device__ __forceinline__ int64_t xcd_remap(int64_t g, int64_t G) {
 }
 
 // ------------------------------------------------------------------ mode product
-// Output tile TM x TN per 256-thread workgroup (4 wave64s in 2 x 2), K chunks of
-// KC staged through padded LDS with a register prefetch of the next chunk; both
-// products of a 1D apply (L X and X R) run in one K loop of length M + Nc, so no
-// intermediate goes to memory.
-// SK (split K): every wave computes the whole tile over its own quarter of each
-// K chunk (independent accumulators per 16 x 16 block instead of one dependent
-// chain), and the four partial tiles are summed through LDS at the end; used for
-// small tiles, whose runtime is the latency of the K loop.
-// NW waves per workgroup (4 in 2 x 2 without split K; 4 or 8 with it).  The
-// split-K partial tiles reuse the LDS of the operand chunks, which are dead by
-// the time the partials are written.
-template <typename T, int TM, int TN, int KC, bool SK = false, int NW = 4>
-struct MpSmem {
-  union {
-    struct {
-      T As[KC][TM + 1];
-      T Bs[KC][TN + 1];
-    } ab;
-    T red[SK ? NW * TM * TN : 1];
-  };
-};
-
 // Work items of one mode product: output tiles x batch items.
 template <int TM, int TN, typename P>
 __host__ __device__ inline int64_t modeprod_items(const P& a) {
   return (int64_t)((a.M + TM - 1) / TM) * ((a.Nc + TN - 1) / TN) * a.nbatch;
-}
-
-// One TM x TN output tile (work item w) of the mode product `a`.
-template <typename T, int TM, int TN, int KC, bool SK = false, int NW = 4>
-__device__ __forceinline__ void modeprod_tile(const ModeProd<T>& a, int64_t w,
-                                              MpSmem<T, TM, TN, KC, SK, NW>& sm) {
-  typedef typename Mma<T>::acc_t acc_t;
-  constexpr int NT = 64 * NW;  // threads per workgroup
-  constexpr int WM = SK ? TM : TM / 2, WN = SK ? TN : TN / 2;
-  constexpr int BM = WM / 16, BN = WN / 16;
-  constexpr int EA = TM * KC / NT, EB = KC * TN / NT;
-  constexpr int KW = SK ? KC / NW : KC;  // K range of one wave within a chunk
-  static_assert(SK || NW == 4, "without split K the four waves form a 2 x 2 grid");
-  static_assert(EA >= 1 && EB >= 1 && EA * NT == TM * KC && EB * NT == KC * TN,
-                "chunk not divisible among the threads");
-  static_assert(KW % 4 == 0, "a wave's K range is a multiple of the MFMA depth");
-  T(&As)[KC][TM + 1] = sm.ab.As;
-  T(&Bs)[KC][TN + 1] = sm.ab.Bs;
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = SK ? 0 : (wave >> 1) * WM, wn = SK ? 0 : (wave & 1) * WN;
-  const int kw0 = SK ? wave * KW : 0;
-  const int tiles_m = (a.M + TM - 1) / TM, tiles_n = (a.Nc + TN - 1) / TN;
-  const int64_t tiles = (int64_t)tiles_m * tiles_n;
-  const int64_t q = w / tiles;
-  const int64_t t = w - q * tiles;
-  const int i0 = (int)(t / tiles_n) * TM, j0 = (int)(t % tiles_n) * TN;
-  const int64_t vec = q / a.per_vec, item = q - vec * a.per_vec;
-  const T* __restrict__ X = a.X + vec * a.ldx + item * a.bstride;
-  T* __restrict__ Y = a.Y + vec * a.ldy + item * a.bstride;
-  const int64_t rs = a.rs;
-  const int M = a.M, Nc = a.Nc;
-
-  acc_t acc[BM][BN];
-#pragma unroll
-  for (int bi = 0; bi < BM; ++bi)
-#pragma unroll
-    for (int bj = 0; bj < BN; ++bj) acc[bi][bj] = acc_t{0, 0, 0, 0};
-
-  const int nL = a.L ? (M + KC - 1) / KC : 0;
-  const int nR = a.R ? (Nc + KC - 1) / KC : 0;
-  const int nchunks = nL + nR;
-  T ra[EA], rb[EB];
-
-  auto load = [&](int c) {
-    if (c < nL) {
-      const int k0 = c * KC;
-#pragma unroll
-      for (int s = 0; s < EA; ++s) {
-        const int e = tid + s * NT, m = e / KC, k = e % KC;
-        const int gi = i0 + m, gk = k0 + k;
-        ra[s] = (gi < M && gk < M) ? a.L[(int64_t)gi * M + gk] : T(0);
-      }
-#pragma unroll
-      for (int s = 0; s < EB; ++s) {
-        const int e = tid + s * NT, k = e / TN, n = e % TN;
-        const int gk = k0 + k, gj = j0 + n;
-        rb[s] = (gk < M && gj < Nc) ? X[(int64_t)gk * rs + gj] : T(0);
-      }
-    } else {
-      const int k0 = (c - nL) * KC;
-#pragma unroll
-      for (int s = 0; s < EA; ++s) {
-        const int e = tid + s * NT, m = e / KC, k = e % KC;
-        const int gi = i0 + m, gk = k0 + k;
-        ra[s] = (gi < M && gk < Nc) ? X[(int64_t)gi * rs + gk] : T(0);
-      }
-#pragma unroll
-      for (int s = 0; s < EB; ++s) {
-        const int e = tid + s * NT, k = e / TN, n = e % TN;
-        const int gk = k0 + k, gj = j0 + n;
-        rb[s] = (gk < Nc && gj < Nc) ? a.R[(int64_t)gk * Nc + gj] : T(0);
-      }
-    }
-  };
-  auto store = [&]() {
-#pragma unroll
-    for (int s = 0; s < EA; ++s) {
-      const int e = tid + s * NT;
-      As[e % KC][e / KC] = ra[s];
-    }
-#pragma unroll
-    for (int s = 0; s < EB; ++s) {
-      const int e = tid + s * NT;
-      Bs[e / TN][e % TN] = rb[s];
-    }
-  };
-
-  if (nchunks > 0) {
-    load(0);
-    store();
-  }
-  __syncthreads();
-  const int lr = lane & 15, lk = lane >> 4;
-  for (int c = 0; c < nchunks; ++c) {
-    if (c + 1 < nchunks) load(c + 1);
-#pragma unroll
-    for (int kk = kw0; kk < kw0 + KW; kk += 4) {
-      T af[BM], bf[BN];
-#pragma unroll
-      for (int bi = 0; bi < BM; ++bi) af[bi] = As[kk + lk][wm + bi * 16 + lr];
-#pragma unroll
-      for (int bj = 0; bj < BN; ++bj) bf[bj] = Bs[kk + lk][wn + bj * 16 + lr];
-#pragma unroll
-      for (int bi = 0; bi < BM; ++bi)
-#pragma unroll
-        for (int bj = 0; bj < BN; ++bj) acc[bi][bj] = Mma<T>::mma(af[bi], bf[bj], acc[bi][bj]);
-    }
-    __syncthreads();
-    if (c + 1 < nchunks) {
-      store();
-      __syncthreads();
-    }
-  }
-
-  // Epilogue: output element (Mma<T>::row(lane/16, r), lane%16) of each
-  // 16 x 16 block.
-  const double shift = a.shifts ? a.shifts[vec] : 0.0;
-  const T* Vp = a.V ? a.V + item * a.bstride : nullptr;
-  auto emit = [&](int gi, int gj, T v) {
-    if (gi < M && gj < Nc) {
-      const int64_t off = (int64_t)gi * rs + gj;
-      if (a.epi == EPI_V) {
-        T pot = (Vp ? Vp[off] : T(0)) - T(shift);
-        v += pot * X[off];
-      } else if (a.epi == EPI_DIV) {
-        v = v / (a.lamL[gi] + a.lamR[gj] + (a.lamItem ? a.lamItem[item] : T(0)) - T(a.sigma));
-      }
-      if (a.acc) v += Y[off];
-      Y[off] = v;
-    }
-  };
-  if constexpr (SK) {
-    // sum the waves' partial tiles (fixed order: deterministic); the operand
-    // chunks are dead here (the K loop ends with a barrier)
-    T* red = sm.red;
-#pragma unroll
-    for (int bi = 0; bi < BM; ++bi)
-#pragma unroll
-      for (int bj = 0; bj < BN; ++bj)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int ri = bi * 16 + Mma<T>::row(lk, r), cj = bj * 16 + lr;
-          red[(wave * TM + ri) * TN + cj] = acc[bi][bj][r];
-        }
-    __syncthreads();
-    for (int e = tid; e < TM * TN; e += NT) {
-      T v = red[e];
-#pragma unroll
-      for (int w2 = 1; w2 < NW; ++w2) v += red[w2 * TM * TN + e];
-      emit(i0 + e / TN, j0 + e % TN, v);
-    }
-    __syncthreads();  // `red` is reused by the next work item of a persistent loop
-  } else {
-#pragma unroll
-    for (int bi = 0; bi < BM; ++bi)
-#pragma unroll
-      for (int bj = 0; bj < BN; ++bj)
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-          emit(i0 + wm + bi * 16 + Mma<T>::row(lk, r), j0 + wn + bj * 16 + lr, acc[bi][bj][r]);
-  }
 }
 
 // ------------------------------------------------------ BF16x3 mode product

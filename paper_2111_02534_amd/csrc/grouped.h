@@ -192,9 +192,10 @@ class TableArena {
 
 // ---- launchers (fixed grid of kPersistWGs workgroups; tables in device memory)
 // Mode products: work items are output tiles (modeprod_items for the tile
-// shape), so a table is built for one tile shape and launched with it.
+// shape), so a table is built for one tile shape and mode (MpMode) and launched
+// with them.
 template <typename T>
-hipError_t launch_modeprod_grouped(DevTab<ModeProd<T>> t, int tile, hipStream_t s);
+hipError_t launch_modeprod_grouped(DevTab<ModeProd<T>> t, int tile, int mode, hipStream_t s);
 hipError_t launch_modeprod_bf3_grouped(DevTab<ModeProd<float>> t, int tile, hipStream_t s);
 int64_t modeprod_items_for(int M, int Nc, int nbatch, int tile, bool bf3);
 

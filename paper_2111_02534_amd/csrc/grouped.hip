@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include "device_bodies.h"
+#include "modeprod.h"
 
 namespace tp3b {
 
@@ -60,24 +61,11 @@ __device__ __forceinline__ void for_wave_items(DevTab<Job> t, int stage, F&& f) 
 }
 
 // ------------------------------------------------------------ mode products
-// At least two waves per SIMD, as for the single-job mode-product kernel.
-template <typename T, int TM, int TN, int KC, bool SK = false>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_modeprod_grouped(
+template <typename T, int MODE, int BM, int BN, int WM, int WN, int SK>
+__global__ __launch_bounds__(64 * WM * WN * SK) __attribute__((amdgpu_waves_per_eu(2))) void k_modeprod_grouped(
     DevTab<ModeProd<T>> t) {
-  __shared__ MpSmem<T, TM, TN, KC, SK> sm;
-  for_wg_items(t, 0, [&](const ModeProd<T>& a, int64_t w) {
-    modeprod_tile<T, TM, TN, KC, SK>(a, w, sm);
-  });
-}
-
-// The small split-K tile with eight waves (same body as the single-job form).
-template <typename T>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k_modeprod_sk8_grouped(
-    DevTab<ModeProd<T>> t) {
-  __shared__ MpSmem<T, 32, 32, 64, true, 8> sm;
-  for_wg_items(t, 0, [&](const ModeProd<T>& a, int64_t w) {
-    modeprod_tile<T, 32, 32, 64, true, 8>(a, w, sm);
-  });
+  __shared__ typename MpTile<T, BM, BN, WM, WN, SK>::Smem sm;
+  for_wg_items(t, 0, [&](const ModeProd<T>& a, int64_t w) { mp_tile<T, BM, BN, WM, WN, SK, MODE>(a, w, sm); });
 }
 
 template <int TM, int TN, int KC>
@@ -99,21 +87,35 @@ int64_t modeprod_items_for(int M, int Nc, int nbatch, int tile, bool bf3) {
   }
 }
 
-template <typename T>
-hipError_t launch_modeprod_grouped(DevTab<ModeProd<T>> t, int tile, hipStream_t s) {
+template <typename T, int MODE>
+static hipError_t launch_mp_grouped(DevTab<ModeProd<T>> t, int tile, hipStream_t s) {
   const dim3 g(kPersistWGs), b(256);
   switch (tile) {
-    case TILE_32: hipLaunchKernelGGL((k_modeprod_grouped<T, 32, 32, 64, true>), g, b, 0, s, t); break;
-    case TILE_32W8: hipLaunchKernelGGL((k_modeprod_sk8_grouped<T>), g, dim3(512), 0, s, t); break;
-    case TILE_64: hipLaunchKernelGGL((k_modeprod_grouped<T, 64, 64, 16>), g, b, 0, s, t); break;
-    case TILE_128: hipLaunchKernelGGL((k_modeprod_grouped<T, 128, 128, 16>), g, b, 0, s, t); break;
-    case TILE_64x128: hipLaunchKernelGGL((k_modeprod_grouped<T, 64, 128, 16>), g, b, 0, s, t); break;
+    case TILE_32: hipLaunchKernelGGL((k_modeprod_grouped<T, MODE, TP3B_MP_32>), g, b, 0, s, t); break;
+    case TILE_32W8: hipLaunchKernelGGL((k_modeprod_grouped<T, MODE, TP3B_MP_32W8>), g, dim3(512), 0, s, t); break;
+    case TILE_64: hipLaunchKernelGGL((k_modeprod_grouped<T, MODE, TP3B_MP_64>), g, b, 0, s, t); break;
+    case TILE_128:
+      if constexpr (sizeof(T) == 4 || MODE < MP_UNFOLD_L)
+        hipLaunchKernelGGL((k_modeprod_grouped<T, MODE, TP3B_MP_128>), g, b, 0, s, t);
+      break;
+    case TILE_64x128: hipLaunchKernelGGL((k_modeprod_grouped<T, MODE, TP3B_MP_64x128>), g, b, 0, s, t); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
-template hipError_t launch_modeprod_grouped<double>(DevTab<ModeProd<double>>, int, hipStream_t);
-template hipError_t launch_modeprod_grouped<float>(DevTab<ModeProd<float>>, int, hipStream_t);
+template <typename T>
+hipError_t launch_modeprod_grouped(DevTab<ModeProd<T>> t, int tile, int mode, hipStream_t s) {
+  tile = tile_of(tile, mode, sizeof(T) == 8);
+  switch (mode) {
+    case MP_FOLD_L: return launch_mp_grouped<T, MP_FOLD_L>(t, tile, s);
+    case MP_FOLD_R: return launch_mp_grouped<T, MP_FOLD_R>(t, tile, s);
+    case MP_UNFOLD_L: return launch_mp_grouped<T, MP_UNFOLD_L>(t, tile, s);
+    case MP_UNFOLD_R: return launch_mp_grouped<T, MP_UNFOLD_R>(t, tile, s);
+    default: return launch_mp_grouped<T, MP_PLAIN>(t, tile, s);
+  }
+}
+template hipError_t launch_modeprod_grouped<double>(DevTab<ModeProd<double>>, int, int, hipStream_t);
+template hipError_t launch_modeprod_grouped<float>(DevTab<ModeProd<float>>, int, int, hipStream_t);
 
 hipError_t launch_modeprod_bf3_grouped(DevTab<ModeProd<float>> t, int tile, hipStream_t s) {
   const dim3 g(kPersistWGs), b(256);

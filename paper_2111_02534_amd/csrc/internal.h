@@ -16,12 +16,18 @@
 
 namespace tp3b {
 
-// Device copies of one operand set in one storage precision.
+// Device copies of one operand set in one storage precision.  The row-major
+// matrices (K, KT, Si, S, SiT, ST) serve the BF16x3 products: FP32 only.
 template <typename T>
 struct DevOps {
   T* K[4] = {nullptr, nullptr, nullptr, nullptr};   // -c D2 of each mode, row-major
   T* KT[4] = {nullptr, nullptr, nullptr, nullptr};  // its transpose (right operand)
   T* V = nullptr;                                   // potential table, vector layout
+  // K, S^{-1} and S of each mode in fragment order (modeprod.h), the last mode as
+  // right operand, the others as left operands; NULL for operators on plane passes
+  T* mK[4] = {nullptr, nullptr, nullptr, nullptr};
+  T* mSi[4] = {nullptr, nullptr, nullptr, nullptr};
+  T* mS[4] = {nullptr, nullptr, nullptr, nullptr};
   // Preconditioner factors per mode: K_k = S_k diag(lam_k) S_k^{-1}.  1D uses
   // modes 0 (x, left operands) and 1 (y, right operands); 2D uses modes 0-2 as
   // left operands and mode 3 as right operand.
@@ -40,6 +46,11 @@ struct DevOps {
   T* frS[4] = {nullptr, nullptr, nullptr, nullptr};
   T* frSi[4] = {nullptr, nullptr, nullptr, nullptr};
   T* G = nullptr;
+  // 1D with reflection-symmetric modes: S_k^{-1} and S_k of the even and the odd
+  // half in fragment order, one after the other, and their eigenvalues likewise
+  T* fSi[2] = {nullptr, nullptr};
+  T* fS[2] = {nullptr, nullptr};
+  T* fLam[2] = {nullptr, nullptr};
 };
 
 // Runs f(i) for every i in [0, n) on up to kHostThreads host threads (the
@@ -102,6 +113,11 @@ struct tp3b_op_s {
   tp3b::DevOps<double> d64;
   tp3b::DevOps<float> d32;
   int work_vecs = 0;
+  // 1D, both mode matrices symmetric under the reflection of their grid: the
+  // preconditioner runs as folded products (MpMode), and the work buffer holds
+  // two blocks of work_vecs vectors of fold_size entries
+  bool fold = false;
+  int64_t fold_size() const { return 4 * (int64_t)tp3b::fold_half(n[0]) * tp3b::fold_row(n[1]); }
   bool plane2d = false;         // 2D with every mode size <= P2_MAXN: two-pass applies
   bool x_same_K = false;        // 2D: the two x modes have the same operator K (and
   bool x_same_S = false;        // the same eigen-factors): one LDS copy in the x passes
@@ -148,7 +164,18 @@ tp3b_status apply_H_impl(tp3b_op op, int nvec, const T* X, int64_t ldx, T* Y, in
 template <typename T>
 tp3b_status apply_prec_impl(tp3b_op op, int nvec, const T* X, int64_t ldx, T* Y, int64_t ldy,
                             hipStream_t s, bool bf3 = false);
-int choose_tile(int M, int Nc, int64_t nbatch, bool fp64);
+// The mode products of a 1D operator for the tile shape they will run with: the
+// Hamiltonian apply, and stage st (0..3) of the preconditioner
+// Z = Sx [(Sx^{-1} B Sy^{-T}) / (lx_i + ly_j - sigma)] Sy^T, whose intermediates
+// live in the operator's work buffer (and, in the plain form, in Y); nv <=
+// work_vecs.
+template <typename T>
+ModeProd<T> h_job(tp3b_op op, int nvec, const T* X, int64_t ldx, T* Y, int64_t ldy, const double* shifts);
+template <typename T>
+ModeProd<T> prec_job(tp3b_op op, int st, int nv, const T* X, int64_t ldx, T* Y, int64_t ldy, bool fold);
+// Whether the preconditioner runs folded (FP64 and FP32).
+bool prec_folded(tp3b_op op, bool bf3);
+int choose_tile(int M, int Nc, int64_t nbatch, bool bf3);
 // Second-derivative matrix (row-major, desc->D2[k] when given) and ascending
 // nodes of mode k of a descriptor.
 void mode_grid(const tp3b_problem_desc* d, int k, std::vector<double>& D2, std::vector<double>& x);

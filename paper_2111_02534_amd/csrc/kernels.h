@@ -40,7 +40,40 @@ struct ModeProd {
   // NULL: the operand is split while it is staged.
   const unsigned short* Lhl;
   const unsigned short* Rhl;
+  // FP64 and FP32 products (modeprod.h): L and R in fragment order
+  // (mp_fragments), used instead of the two above.
+  const T* LF;
+  const T* RF;
+  // Folded products (mode other than MP_PLAIN): the even factor at LF or RF, the
+  // odd one fq entries on; size of the folded mode; the output's row stride
+  // (bstride is the output's item stride); unfold: where the odd operand lies
+  // behind the even one; fold: EPI_DIV reads lamR + item lamRq.
+  int mode;
+  int full;
+  int64_t fq, rsy, oddx;
+  int lamRq;
 };
+
+// A mode matrix that commutes with the reflection of its grid (K[i][j] =
+// K[n-1-i][n-1-j], as every second-derivative matrix on a grid symmetric about 0
+// does) has even and odd eigenvectors only.  On the sums and differences of
+// mirrored entries,
+//   s_j = x_j + x_{j'}, d_j = x_j - x_{j'}   (j' = n-1-j, j < h = ceil(n/2)),
+// a transform into or out of its eigenbasis is two products of size h instead of
+// one of size n, half the work: z_even = E s, z_odd = O d into the basis, and
+// u = E z_even, v = O z_odd, x_j = u_j + v_j, x_{j'} = u_j - v_j out of it.  (The
+// middle entry of an odd n is its own mirror: it counts twice in s, which the
+// halves in the forward factors make up for, and is zero in d.)  The four
+// products of a preconditioner apply fold on the way in and unfold on the way
+// out:
+//   MP_FOLD_L    Y[p] = F_p (X[i] +- X[i']), p = 0, 1 (items), rows h_x each
+//   MP_FOLD_R    Y[.., p] = (X[.., j] +- X[.., j']) F_p^T, rows 2 h_x
+//   MP_UNFOLD_L  Y[i], Y[i'] = F_0 X[0] +- F_1 X[1]
+//   MP_UNFOLD_R  Y[.., j], Y[.., j'] = X[.., 0] F_0^T +- X[.., 1] F_1^T
+// with rows of the y halves fold_row(n_y) apart.
+enum MpMode { MP_PLAIN = 0, MP_FOLD_L = 1, MP_FOLD_R = 2, MP_UNFOLD_L = 3, MP_UNFOLD_R = 4 };
+__host__ __device__ inline int fold_half(int n) { return (n + 1) / 2; }
+__host__ __device__ inline int fold_row(int n) { return (fold_half(n) + 3) / 4 * 4; }
 
 // Tile configurations (output tile TM x TN per 256-thread workgroup; the
 // 32 x 32 tiles split the K range over their waves, TILE_32W8 over eight waves
@@ -53,7 +86,15 @@ enum TileCfg {
   TILE_32W8 = 4,
   NUM_TILE_CFGS = 5
 };
-inline int tile_rows(int tile) { return (tile == TILE_32 || tile == TILE_32W8) ? 32 : (tile == TILE_128 ? 128 : 64); }
+// The tile that a product of mode `mode` runs with: an unfolding product holds two
+// sets of accumulators, which in FP64 do not fit the registers at 128 x 128.
+inline int tile_of(int tile, int mode, bool fp64) {
+  return fp64 && tile == TILE_128 && (mode == MP_UNFOLD_L || mode == MP_UNFOLD_R) ? (int)TILE_64x128 : tile;
+}
+// Output rows and columns of a workgroup's tile.
+inline int tile_rows(int tile) {
+  return (tile == TILE_32 || tile == TILE_32W8) ? 32 : (tile == TILE_128 ? 128 : 64);
+}
 inline int tile_cols(int tile) {
   return (tile == TILE_32 || tile == TILE_32W8) ? 32 : ((tile == TILE_64) ? 64 : 128);
 }

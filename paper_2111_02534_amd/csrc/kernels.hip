@@ -16,9 +16,11 @@
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "device_bodies.h"
+#include "modeprod.h"
 
 namespace tp3b {
 
@@ -44,43 +46,43 @@ LaunchTiming*& launch_timing() {
 // ROLE only separates the kernel names seen by profilers: 0 = Hamiltonian apply
 // (both modes + potential), 1 = preconditioner mode products, 2 = 2D x-mode
 // accumulation passes.
-// At least two waves per SIMD: with one (the register demand of the FP64
-// 128 x 128 tile left to itself) every barrier and fetch of the K loop is
-// exposed; measured on c3, the best FP64 tile goes from 1.42 to 1.23 ms.
-template <typename T, int TM, int TN, int KC, int ROLE, bool SK = false>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_modeprod(ModeProd<T> a) {
-  __shared__ MpSmem<T, TM, TN, KC, SK> sm;
-  modeprod_tile<T, TM, TN, KC, SK>(a, xcd_remap(blockIdx.x, modeprod_items<TM, TN>(a)), sm);
-}
-
-// Small grids: 32 x 32 output tile split over the K of eight waves (512
-// threads, K-chunks of 64), four waves per SIMD.
-template <typename T, int ROLE>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k_modeprod_sk8(
+template <typename T, int ROLE, int MODE, int BM, int BN, int WM, int WN, int SK>
+__global__ __launch_bounds__(64 * WM * WN * SK) __attribute__((amdgpu_waves_per_eu(2))) void k_modeprod(
     ModeProd<T> a) {
-  __shared__ MpSmem<T, 32, 32, 64, true, 8> sm;
-  modeprod_tile<T, 32, 32, 64, true, 8>(a, xcd_remap(blockIdx.x, modeprod_items<32, 32>(a)), sm);
+  typedef MpTile<T, BM, BN, WM, WN, SK> G;
+  __shared__ typename G::Smem sm;
+  mp_tile<T, BM, BN, WM, WN, SK, MODE>(a, xcd_remap(blockIdx.x, modeprod_items<G::TM, G::TN>(a)), sm);
 }
 
-template <typename T, int ROLE>
-static void launch_role(const ModeProd<T>& a, int tile, hipStream_t s, unsigned g32, unsigned g64,
-                        unsigned g128, unsigned g64x128) {
+// Whether the kernel's 32-bit byte offsets reach every row that a chunk of the
+// tile spans.
+template <typename G, typename T>
+static bool mp_reach(const ModeProd<T>& a) {
+  const int64_t rows = std::max(a.LF ? (int)G::KT : 1, a.RF ? (int)G::TM : 1);
+  return rows * a.rs * (int64_t)sizeof(T) + 256 * 1024 < (int64_t)1 << 32;
+}
+
+template <typename T, int ROLE, int MODE, int BM, int BN, int WM, int WN, int SK>
+static void launch_mp(const ModeProd<T>& a, hipStream_t s) {
+  typedef MpTile<T, BM, BN, WM, WN, SK> G;
+  if constexpr (SK > 1) {
+    // (rows of a long 2D vector: a tile with shorter chunks)
+    if (!mp_reach<G>(a)) return launch_mp<T, ROLE, MODE, TP3B_MP_64>(a, s);
+  }
+  const unsigned grid = (unsigned)modeprod_items<G::TM, G::TN>(a);
+  TP3B_MP_LAUNCH((k_modeprod<T, ROLE, MODE, BM, BN, WM, WN, SK>), grid, G::NT, s, a);
+}
+
+template <typename T, int ROLE, int MODE>
+static void launch_role(const ModeProd<T>& a, int tile, hipStream_t s) {
   switch (tile) {
-    case TILE_32:
-      TP3B_MP_LAUNCH((k_modeprod<T, 32, 32, 64, ROLE, true>), g32, 256, s, a);
-      break;
-    case TILE_32W8:
-      TP3B_MP_LAUNCH((k_modeprod_sk8<T, ROLE>), g32, 512, s, a);
-      break;
-    case TILE_64:
-      TP3B_MP_LAUNCH((k_modeprod<T, 64, 64, 16, ROLE>), g64, 256, s, a);
-      break;
+    case TILE_32: launch_mp<T, ROLE, MODE, TP3B_MP_32>(a, s); break;
+    case TILE_32W8: launch_mp<T, ROLE, MODE, TP3B_MP_32W8>(a, s); break;
+    case TILE_64: launch_mp<T, ROLE, MODE, TP3B_MP_64>(a, s); break;
     case TILE_128:
-      TP3B_MP_LAUNCH((k_modeprod<T, 128, 128, 16, ROLE>), g128, 256, s, a);
+      if constexpr (sizeof(T) == 4 || MODE < MP_UNFOLD_L) launch_mp<T, ROLE, MODE, TP3B_MP_128>(a, s);
       break;
-    default:
-      TP3B_MP_LAUNCH((k_modeprod<T, 64, 128, 16, ROLE>), g64x128, 256, s, a);
-      break;
+    default: launch_mp<T, ROLE, MODE, TP3B_MP_64x128>(a, s); break;
   }
 }
 
@@ -88,17 +90,22 @@ template <typename T>
 hipError_t launch_modeprod(const ModeProd<T>& a, int tile, hipStream_t s) {
   if (a.M <= 0 || a.Nc <= 0 || a.nbatch <= 0) return hipSuccess;
   if (tile < 0 || tile >= NUM_TILE_CFGS) return hipErrorInvalidValue;
-  auto grid = [&](int TM, int TN) {
-    int64_t tiles = (int64_t)((a.M + TM - 1) / TM) * ((a.Nc + TN - 1) / TN);
-    return (unsigned)(tiles * a.nbatch);
-  };
-  const unsigned g32 = grid(32, 32), g64 = grid(64, 64), g128 = grid(128, 128), g6412 = grid(64, 128);
-  if (a.L && a.R && a.epi == EPI_V)
-    launch_role<T, 0>(a, tile, s, g32, g64, g128, g6412);
-  else if (a.acc)
-    launch_role<T, 2>(a, tile, s, g32, g64, g128, g6412);
-  else
-    launch_role<T, 1>(a, tile, s, g32, g64, g128, g6412);
+  if (!a.LF && !a.RF) return hipErrorInvalidValue;
+  tile = tile_of(tile, a.mode, sizeof(T) == 8);
+  if (!mp_reach<MpTile<T, TP3B_MP_128>>(a)) return hipErrorInvalidValue;  // N of 10^10 and more
+  switch (a.mode) {
+    case MP_FOLD_L: launch_role<T, 1, MP_FOLD_L>(a, tile, s); break;
+    case MP_FOLD_R: launch_role<T, 1, MP_FOLD_R>(a, tile, s); break;
+    case MP_UNFOLD_L: launch_role<T, 1, MP_UNFOLD_L>(a, tile, s); break;
+    case MP_UNFOLD_R: launch_role<T, 1, MP_UNFOLD_R>(a, tile, s); break;
+    default:
+      if (a.LF && a.RF && a.epi == EPI_V)
+        launch_role<T, 0, MP_PLAIN>(a, tile, s);
+      else if (a.acc)
+        launch_role<T, 2, MP_PLAIN>(a, tile, s);
+      else
+        launch_role<T, 1, MP_PLAIN>(a, tile, s);
+  }
   return hipGetLastError();
 }
 

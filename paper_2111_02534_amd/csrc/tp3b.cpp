@@ -48,6 +48,27 @@ tp3b_status exception_status() {
 }
 
 // ---------------------------------------------------------------- grids
+// The grids are symmetric about 0, so a second-derivative matrix commutes with
+// the reflection, D2[i][j] = D2[n-1-i][n-1-j].  Its upper half of rows is
+// computed and the lower half copied from it, so that the symmetry holds bit
+// for bit (the middle row of an odd n takes its left half) and the products
+// may use it (fold.h).
+static void mirror_rows(int n, std::vector<double>& D2) {
+  for (int i = 0; i < (n + 1) / 2; ++i)
+    for (int j = 0; j < n; ++j) {
+      const int i2 = n - 1 - i, j2 = n - 1 - j;
+      if (i2 != i || j2 > j) D2[(size_t)i2 * n + j2] = D2[(size_t)i * n + j];
+    }
+}
+
+// Whether A[i][j] == A[n-1-i][n-1-j] for every entry.
+static bool reflection_symmetric(int n, const std::vector<double>& A) {
+  const size_t nn = (size_t)n * n;
+  for (size_t e = 0; e < nn / 2; ++e)
+    if (!(A[e] == A[nn - 1 - e])) return false;
+  return true;
+}
+
 // Second-derivative collocation matrix on the n interior Chebyshev-Gauss-Lobatto
 // points of [-L, L] with homogeneous Dirichlet conditions (Sec. 3.1): the
 // Lagrange interpolant through K+1 = n+2 points t_j = cos(pi j/K) is
@@ -74,12 +95,13 @@ static void cgl_second_derivative(int n, double L, std::vector<double>& D2,
   }
   D2.assign((size_t)n * n, 0.0);
   const double s = 1.0 / (L * L);
-  for (int i = 1; i <= n; ++i)
+  for (int i = 1; i <= (n + 1) / 2; ++i)
     for (int j = 1; j <= n; ++j) {
       double acc = 0.0;
       for (int k = 0; k <= K; ++k) acc += D[(size_t)i * (K + 1) + k] * D[(size_t)k * (K + 1) + j];
       D2[(size_t)(i - 1) * n + (j - 1)] = acc * s;
     }
+  mirror_rows(n, D2);
   x.resize(n);
   for (int i = 1; i <= n; ++i) x[i - 1] = -L * t[i];
 }
@@ -116,13 +138,14 @@ static void mapped_second_derivative(int N, double L, std::vector<double>& D2,
     const double s = 1.0 - t[i] * t[i];
     const double tp = s * std::sqrt(s) / L;
     const double tpp = -3.0 * t[i] * s * s / (L * L);
-    for (int j = 0; j < N; ++j) {
+    for (int j = 0; i < (N + 1) / 2 && j < N; ++j) {
       double dd = 0.0;
       for (int k = 0; k < N; ++k) dd += D[(size_t)i * N + k] * D[(size_t)k * N + j];
       D2[(size_t)i * N + j] = tp * tp * dd + tpp * D[(size_t)i * N + j];
     }
     x[i] = L * t[i] / std::sqrt(s);
   }
+  mirror_rows(N, D2);
 }
 
 // Restriction of an operator on a grid symmetric about 0 (an even number N of
@@ -174,27 +197,27 @@ void mode_grid(const tp3b_problem_desc* d, int k, std::vector<double>& D2, std::
   if (d->D2[k]) D2.assign(d->D2[k], d->D2[k] + (size_t)n * n);
 }
 
-int choose_tile(int M, int Nc, int64_t nbatch, bool fp64) {
-  // Largest tile that still gives >= 1024 workgroups (4 per CU); otherwise the
-  // one giving the most parallelism without mostly-empty tiles.
-  struct C { int id, tm, tn; };
-  // Of the two 32 x 32 tiles the eight-wave form: twice the waves in flight
-  // per tile to cover the MFMA and fetch latencies of a short K loop (measured
-  // at n = 256, 8 vectors: H apply 20.8 against 22.8 us in FP64, 14.4 against
-  // 16.4 us in FP32).
-  // FP64 skips the 128-wide tiles: under the two-waves-per-SIMD bound their
-  // accumulators spill (n = 1024, 16 vectors: 64 x 64 1.23 ms, 64 x 128
-  // 1.34 ms, 128 x 128 1.41 ms per H apply).
-  const int small = TILE_32W8;
-  const C cfgs[] = {{TILE_128, 128, 128}, {TILE_64x128, 64, 128}, {TILE_64, 64, 64}, {small, 32, 32}};
-  for (const C& c : cfgs) {
-    if (c.tm > M || c.tn > Nc) continue;
-    if (fp64 && c.tn > 64) continue;
-    int64_t wg = (int64_t)((M + c.tm - 1) / c.tm) * ((Nc + c.tn - 1) / c.tn) * nbatch;
-    if (wg >= 1024) return c.id;
-  }
-  return (M >= 64 && Nc >= 64 && (int64_t)((M + 63) / 64) * ((Nc + 63) / 64) * nbatch >= 512) ? TILE_64
-                                                                                            : small;
+static int choose_tile_bf3(int M, int Nc, int64_t nbatch) {
+  // largest tile that still gives >= 1024 workgroups (4 per CU)
+  auto wg = [&](int64_t tm, int64_t tn) { return ((M + tm - 1) / tm) * ((Nc + tn - 1) / tn) * nbatch; };
+  if (M >= 128 && Nc >= 128 && wg(128, 128) >= 1024) return TILE_128;
+  if (M >= 64 && Nc >= 128 && wg(64, 128) >= 1024) return TILE_64x128;
+  return TILE_64;
+}
+
+int choose_tile(int M, int Nc, int64_t nbatch, bool bf3) {
+  if (bf3) return choose_tile_bf3(M, Nc, nbatch);
+  // The largest tile that still fills the chip; below that the 32 x 32 tile whose
+  // four waves split the K range.  Us per H apply (FP64, FP32) by tile:
+  //                         32 x 32       64 x 64      64 x 128      128 x 128
+  //   1024 x 1024 x 16   1232 / 671    1017 / 499    956 / 493     957 / 495
+  //   512 x 512 x 8        75.8 / 44.7   71.0 / 38.7   74.7 / 40.5  129.9 / 69.0
+  //   256 x 256 x 8        14.2 /  9.2   22.0 / 13.0   37.1 / 21.4   67.0 / 37.3
+  // (BF16x3 has 64 x 64 and more.)
+  auto wg = [&](int64_t tm, int64_t tn) { return ((M + tm - 1) / tm) * ((Nc + tn - 1) / tn) * nbatch; };
+  if (M >= 64 && Nc >= 128 && wg(64, 128) >= 1024) return TILE_64x128;
+  if (M >= 64 && Nc >= 64 && wg(64, 64) >= 384) return TILE_64;
+  return TILE_32;
 }
 
 // --------------------------------------------------------------- scratch
@@ -240,7 +263,8 @@ static void free_ops(tp3b::DevOps<T>& d) {
       if (p) (void)hipFree(p);
   }
   for (int k = 0; k < 4; ++k) {
-    T* fs[] = {d.frK[k], d.frS[k], d.frSi[k]};
+    T* fs[] = {d.mK[k], d.mSi[k], d.mS[k], d.frK[k], d.frS[k], d.frSi[k], k < 2 ? d.fS[k] : nullptr, k < 2 ? d.fSi[k] : nullptr,
+               k < 2 ? d.fLam[k] : nullptr};
     for (T* p : fs)
       if (p) (void)hipFree(p);
   }
@@ -260,27 +284,97 @@ static std::vector<double> transpose(const std::vector<double>& A, int n) {
 // Host eigen-factors of the kinetic mode operators K_k = S_k diag(lam_k) S_k^{-1}.
 struct PrecFactors {
   std::vector<double> S[4], Si[4], lam[4];
+  // reflection-symmetric modes: the factors of the even [0] and odd [1] half,
+  // ceil(n/2) and floor(n/2) wide (lam holds the even eigenvalues first)
+  std::vector<double> SF[4][2], SiF[4][2];
   std::vector<double> lamItem;   // 2D: lam_0[i1] + lam_1[i2]
   std::vector<double> lamItemY;  // 2D: lam_2[j1] + lam_3[j2]
 };
 
+// Eigen-factors of a reflection-symmetric mode operator from those of its even
+// and odd halves (a quarter of the work of the whole matrix): the even
+// eigenvectors are (u, u mirrored), the odd ones (u, -u mirrored).
+static bool parity_decompose(int n, const std::vector<double>& K, PrecFactors& pf, int k) {
+  const int h[2] = {(n + 1) / 2, n / 2};
+  pf.S[k].assign((size_t)n * n, 0.0);
+  pf.Si[k].assign((size_t)n * n, 0.0);
+  pf.lam[k].resize(n);
+  for (int p = 0; p < 2; ++p) {
+    const int m = h[p], c0 = p ? h[0] : 0;
+    const double sg = p ? -1.0 : 1.0;
+    if (m == 0) continue;
+    std::vector<double> A((size_t)m * m);
+    for (int i = 0; i < m; ++i)
+      for (int j = 0; j < m; ++j)
+        A[(size_t)i * m + j] = K[(size_t)i * n + j] + (n - 1 - j != j ? sg * K[(size_t)i * n + n - 1 - j] : 0.0);
+    std::vector<double>&S = pf.SF[k][p], &Si = pf.SiF[k][p];
+    S.resize((size_t)m * m);
+    Si.resize((size_t)m * m);
+    if (!eigen_decompose_real(m, A.data(), S.data(), Si.data(), pf.lam[k].data() + c0)) return false;
+    for (int i = 0; i < m; ++i) {
+      const int i2 = n - 1 - i;
+      for (int c = 0; c < m; ++c) {
+        pf.S[k][(size_t)i * n + c0 + c] = S[(size_t)i * m + c];
+        if (i2 != i) pf.S[k][(size_t)i2 * n + c0 + c] = sg * S[(size_t)i * m + c];
+        const double v = Si[(size_t)c * m + i] * (i2 != i ? 0.5 : 1.0);
+        pf.Si[k][(size_t)(c0 + c) * n + i] = v;
+        if (i2 != i) pf.Si[k][(size_t)(c0 + c) * n + i2] = sg * v;
+      }
+    }
+  }
+  return true;
+}
+
+// A mode matrix in the fragment order of modeprod.h: for every K group (8 k in
+// FP64, 16 in FP32) and block of 16 rows a 16-byte piece per lane, lane l holding
+// columns KU (l / 16) + u of the group.  As left operand (A X) block b lane l is
+// row 16 b + l % 16; as right operand (X A^T) the columns of A^T are dealt in
+// pairs, block 2 g + b lane l holding 32 g + 2 (l % 16) + b.
+template <typename T>
+static void mp_fragments(int n, const double* A, bool right, std::vector<double>& out, int ld = 0) {
+  constexpr int KU = 16 / (int)sizeof(T);
+  const int rows = (n + 31) / 32 * 32, kp = (n + 15) / 16 * 16;
+  if (!ld) ld = n;
+  const size_t at = out.size();
+  out.resize(at + (size_t)rows * kp, 0.0);
+  for (int i = 0; i < n; ++i) {
+    const int blk = right ? 2 * (i / 32) + i % 2 : i / 16, lr = right ? (i % 32) / 2 : i % 16;
+    for (int k = 0; k < n; ++k) {
+      const int kg = k / (4 * KU), lk = k % (4 * KU) / KU, u = k % KU;
+      out[at + (((size_t)kg * (rows / 16) + blk) * 64 + lk * 16 + lr) * KU + u] = A[(size_t)i * ld + k];
+    }
+  }
+}
+
 template <typename T>
 static tp3b_status upload_ops(tp3b_op op, tp3b::DevOps<T>& d, const std::vector<double>* Kh,
                               const PrecFactors& pf) {
-  for (int k = 0; k < op->nmodes; ++k) {
-    TP3B_HIP(upload(&d.K[k], Kh[k]));
-    TP3B_HIP(upload(&d.KT[k], transpose(Kh[k], op->n[k])));
+  const int last = op->nmodes - 1;  // applied from the right, the others from the left
+  if (sizeof(T) == 4) {
+    for (int k = 0; k < op->nmodes; ++k) {
+      TP3B_HIP(upload(&d.K[k], Kh[k]));
+      TP3B_HIP(upload(&d.KT[k], transpose(Kh[k], op->n[k])));
+    }
+  }
+  std::vector<double> F;
+  auto fragments = [&](T** dst, int k, const std::vector<double>& A) -> hipError_t {
+    F.clear();
+    mp_fragments<T>(op->n[k], A.data(), k == last, F);
+    return upload(dst, F);
+  };
+  for (int k = 0; k < op->nmodes && !op->plane2d; ++k) {
+    TP3B_HIP(fragments(&d.mK[k], k, Kh[k]));
+    if (!op->have_prec) continue;
+    TP3B_HIP(fragments(&d.mSi[k], k, pf.Si[k]));
+    TP3B_HIP(fragments(&d.mS[k], k, pf.S[k]));
   }
   TP3B_HIP(upload(&d.V, op->Vh));
   if (op->have_prec) {
-    // the last mode is applied from the right (transposed factors), the others
-    // from the left
-    const int last = op->nmodes - 1;
     for (int k = 0; k < op->nmodes; ++k) {
-      if (k < last) {
+      if (sizeof(T) == 4 && k < last) {
         TP3B_HIP(upload(&d.Si[k], pf.Si[k]));
         TP3B_HIP(upload(&d.S[k], pf.S[k]));
-      } else {
+      } else if (sizeof(T) == 4) {
         TP3B_HIP(upload(&d.SiT[k], transpose(pf.Si[k], op->n[k])));
         TP3B_HIP(upload(&d.ST[k], transpose(pf.S[k], op->n[k])));
       }
@@ -290,7 +384,35 @@ static tp3b_status upload_ops(tp3b_op op, tp3b::DevOps<T>& d, const std::vector<
       TP3B_HIP(upload(&d.lamItem, pf.lamItem));
       TP3B_HIP(upload(&d.lamItemY, pf.lamItemY));
     }
-    TP3B_HIP(hipMalloc((void**)&d.work, sizeof(T) * op->N * op->work_vecs));
+    // 1D with folded products: two blocks
+    const int64_t per = op->fold ? std::max(op->N, 2 * op->fold_size()) : op->N;
+    TP3B_HIP(hipMalloc((void**)&d.work, sizeof(T) * per * op->work_vecs));
+  }
+  if (op->fold && op->have_prec) {
+    for (int k = 0; k < 2; ++k) {
+      const int n = op->n[k], h = fold_half(n), ho = n / 2;
+      // into the eigenbasis (half of the sums and differences) and back; the odd
+      // half of an odd n is one shorter and padded with zeros
+      std::vector<double> A((size_t)h * h), Fi;
+      F.clear();
+      for (int p = 0; p < 2; ++p) {
+        const int m = p ? ho : h;
+        for (int side = 0; side < 2; ++side) {
+          std::fill(A.begin(), A.end(), 0.0);
+          for (int i = 0; i < m; ++i)
+            for (int j = 0; j < m; ++j)
+              A[(size_t)i * h + j] = side ? pf.SF[k][p][(size_t)i * m + j] : 0.5 * pf.SiF[k][p][(size_t)i * m + j];
+          mp_fragments<T>(h, A.data(), k == 1, side ? F : Fi);
+        }
+      }
+      TP3B_HIP(upload(&d.fSi[k], Fi));
+      TP3B_HIP(upload(&d.fS[k], F));
+      // eigenvalues, even then odd, the odd ones of an odd n padded by one (that
+      // entry is zero whatever it is divided by)
+      std::vector<double> lam((size_t)2 * h, pf.lam[k][0]);
+      std::copy(pf.lam[k].begin(), pf.lam[k].end(), lam.begin());
+      TP3B_HIP(upload(&d.fLam[k], lam));
+    }
   }
   if (op->plane2d) {
     std::vector<double> F(tp3b::P2_FRAG);
@@ -325,10 +447,12 @@ static int tile_for(tp3b_op op, bool f64, bool bf3, int kind, int M, int Nc, int
   if (op->tile_override >= 0) return op->tile_override;
   const int t = op->tuned[prec_index(f64, bf3)][kind];
   if (t >= 0) return t;
-  return choose_tile(M, Nc, nbatch, f64);
+  return choose_tile(M, Nc, nbatch, bf3);
 }
 
 int op_tile(tp3b_op op, bool f64, bool bf3, int kind, int64_t nbatch) {
+  if (kind == 1 && prec_folded(op, bf3))
+    return tile_for(op, f64, bf3, kind, fold_half(op->n[0]), op->n[1], 2 * nbatch);
   return tile_for(op, f64, bf3, kind, op->n[0], op->n[1], nbatch);
 }
 
@@ -384,30 +508,111 @@ template <typename T>
 static tp3b::DevOps<T>& ops_for(tp3b_op op) { return dev_ops<T>(op); }
 
 template <typename T>
+ModeProd<T> h_job(tp3b_op op, int nvec, const T* X, int64_t ldx, T* Y, int64_t ldy, const double* shifts) {
+  DevOps<T>& d = dev_ops<T>(op);
+  ModeProd<T> a{};
+  a.M = op->n[0];
+  a.Nc = op->n[1];
+  a.rs = op->n[1];
+  a.ldx = ldx;
+  a.ldy = ldy;
+  a.per_vec = 1;
+  a.nbatch = nvec;
+  a.X = X;
+  a.Y = Y;
+  a.V = d.V;
+  a.shifts = shifts;
+  a.epi = EPI_V;
+  a.L = d.K[0]; a.LF = d.mK[0];
+  a.R = d.KT[1]; a.RF = d.mK[1];
+  return a;
+}
+
+// Small grids keep the plain products: their four launches are bound by latency,
+// which the folds add to.  Us per apply, plain / folded: 128 x 128 x 8 19.2 / 19.8
+// (FP32 17.4 / 19.4), 256 x 128 x 4 22.1 / 23.2, 256 x 256 x 8 36.9 / 30.7 (FP32
+// 26.2 / 22.0), 512 x 512 x 8 156 / 108, 1024 x 1024 x 16 1953 / 1097.
+bool prec_folded(tp3b_op op, bool bf3) { return op->fold && !bf3 && op->N > 32768; }
+
+template <typename T>
+ModeProd<T> prec_job(tp3b_op op, int st, int nv, const T* X, int64_t ldx, T* Y, int64_t ldy, bool fold) {
+  DevOps<T>& d = dev_ops<T>(op);
+  ModeProd<T> a{};
+  a.M = op->n[0];
+  a.Nc = op->n[1];
+  a.rs = op->n[1];
+  a.per_vec = 1;
+  a.nbatch = nv;
+  a.sigma = op->sigma;
+  a.epi = EPI_NONE;
+  if (fold) {
+    // stages 0 and 3 read X and write Y; in between the two halves of the work
+    // buffer hold, per vector, the rows of both x parities (2 h_x) by n_y padded
+    // to 4, then by the columns of both y parities, then all rows by those
+    const int nx = op->n[0], ny = op->n[1], hx = fold_half(nx), hy = fold_half(ny), ry = fold_row(ny);
+    const int64_t nc4 = (ny + 3) / 4 * 4, sz = op->fold_size();
+    T* w0 = d.work;
+    T* w1 = d.work + sz * op->work_vecs;
+    a.ldx = a.ldy = sz;
+    const int k = st % 2, h = k ? hy : hx;
+    (k ? a.RF : a.LF) = st < 2 ? d.fSi[k] : d.fS[k];
+    a.fq = (int64_t)((h + 31) / 32 * 32) * ((h + 15) / 16 * 16);
+    a.full = k ? ny : nx;
+    switch (st) {
+      case 0:
+        a.mode = MP_FOLD_L;
+        a.M = hx; a.Nc = ny; a.rs = ny; a.rsy = nc4;
+        a.X = X; a.ldx = ldx; a.Y = w0;
+        a.bstride = hx * nc4; a.per_vec = 2; a.nbatch = 2 * nv;
+        break;
+      case 1:
+        a.mode = MP_FOLD_R;
+        a.M = 2 * hx; a.Nc = hy; a.rs = nc4; a.rsy = 2 * ry;
+        a.X = w0; a.Y = w1;
+        a.bstride = ry; a.per_vec = 2; a.nbatch = 2 * nv;
+        a.epi = EPI_DIV; a.lamL = d.fLam[0]; a.lamR = d.fLam[1]; a.lamRq = hy;
+        break;
+      case 2:
+        a.mode = MP_UNFOLD_L;
+        a.M = hx; a.Nc = 2 * ry; a.rs = a.rsy = 2 * ry;
+        a.X = w1; a.Y = w0; a.oddx = (int64_t)hx * 2 * ry;
+        break;
+      default:
+        a.mode = MP_UNFOLD_R;
+        a.M = nx; a.Nc = hy; a.rs = 2 * ry; a.rsy = ny;
+        a.X = w0; a.Y = Y; a.ldy = ldy; a.oddx = ry;
+        break;
+    }
+    return a;
+  }
+  const int64_t N = op->N;
+  switch (st) {
+    case 0: a.X = X; a.ldx = ldx; a.Y = d.work; a.ldy = N; a.L = d.Si[0]; a.LF = d.mSi[0]; break;
+    case 1:
+      a.X = d.work; a.ldx = N; a.Y = Y; a.ldy = ldy; a.R = d.SiT[1]; a.RF = d.mSi[1];
+      a.epi = EPI_DIV; a.lamL = d.lam[0]; a.lamR = d.lam[1];
+      break;
+    case 2: a.X = Y; a.ldx = ldy; a.Y = d.work; a.ldy = N; a.L = d.S[0]; a.LF = d.mS[0]; break;
+    default: a.X = d.work; a.ldx = N; a.Y = Y; a.ldy = ldy; a.R = d.ST[1]; a.RF = d.mS[1]; break;
+  }
+  return a;
+}
+#define TP3B_JOBS(T)                                                                                  \
+  template ModeProd<T> h_job<T>(tp3b_op, int, const T*, int64_t, T*, int64_t, const double*);          \
+  template ModeProd<T> prec_job<T>(tp3b_op, int, int, const T*, int64_t, T*, int64_t, bool);
+TP3B_JOBS(double)
+TP3B_JOBS(float)
+#undef TP3B_JOBS
+
+template <typename T>
 tp3b_status apply_H_impl(tp3b_op op, int nvec, const T* X, int64_t ldx, T* Y, int64_t ldy,
                          const double* shifts, hipStream_t s, bool bf3) {
   tp3b::DevOps<T>& d = ops_for<T>(op);
   const bool f64 = sizeof(T) == 8;
   if (op->ndim == 1) {
     // Y = K_x W + W K_y^T + (V - shift) o W per vector (eq. (10)).
-    ModeProd<T> a{};
-    a.M = op->n[0];
-    a.Nc = op->n[1];
-    a.rs = op->n[1];
-    a.bstride = 0;
-    a.ldx = ldx;
-    a.ldy = ldy;
-    a.per_vec = 1;
-    a.nbatch = nvec;
-    a.X = X;
-    a.Y = Y;
-    a.L = d.K[0];
-    a.R = d.KT[1];
-    a.V = d.V;
-    a.shifts = shifts;
-    a.epi = EPI_V;
-    a.acc = 0;
-    TP3B_HIP(modeprod(op, a, tile_for(op, f64, bf3, 0, a.M, a.Nc, nvec), s, bf3));
+    const int tile = tile_for(op, f64, bf3, 0, op->n[0], op->n[1], nvec);
+    TP3B_HIP(modeprod(op, h_job<T>(op, nvec, X, ldx, Y, ldy, shifts), tile, s, bf3));
     return TP3B_OK;
   }
   const int nx1 = op->n[0], nx2 = op->n[1], ny1 = op->n[2], ny2 = op->n[3];
@@ -474,13 +679,13 @@ tp3b_status apply_H_impl(tp3b_op op, int nvec, const T* X, int64_t ldx, T* Y, in
     a.nbatch = nvec * nx1 * nx2;
     a.X = X;
     a.Y = Y;
-    a.L = d.K[2];
-    a.R = d.KT[3];
+    a.L = d.K[2]; a.LF = d.mK[2];
+    a.R = d.KT[3]; a.RF = d.mK[3];
     a.V = d.V;
     a.shifts = shifts;
     a.epi = EPI_V;
     a.acc = 0;
-    int tile = op->tile_override >= 0 ? op->tile_override : choose_tile(a.M, a.Nc, a.nbatch, f64);
+    int tile = op->tile_override >= 0 ? op->tile_override : choose_tile(a.M, a.Nc, a.nbatch, bf3);
     TP3B_HIP(modeprod(op, a, tile, s, bf3));
   }
   {
@@ -495,11 +700,11 @@ tp3b_status apply_H_impl(tp3b_op op, int nvec, const T* X, int64_t ldx, T* Y, in
     a.nbatch = nvec * nx1;
     a.X = X;
     a.Y = Y;
-    a.L = d.K[1];
+    a.L = d.K[1]; a.LF = d.mK[1];
     a.R = nullptr;
     a.epi = EPI_NONE;
     a.acc = 1;
-    int tile = op->tile_override >= 0 ? op->tile_override : choose_tile(a.M, a.Nc, a.nbatch, f64);
+    int tile = op->tile_override >= 0 ? op->tile_override : choose_tile(a.M, a.Nc, a.nbatch, bf3);
     TP3B_HIP(modeprod(op, a, tile, s, bf3));
   }
   {
@@ -514,11 +719,11 @@ tp3b_status apply_H_impl(tp3b_op op, int nvec, const T* X, int64_t ldx, T* Y, in
     a.nbatch = nvec;
     a.X = X;
     a.Y = Y;
-    a.L = d.K[0];
+    a.L = d.K[0]; a.LF = d.mK[0];
     a.R = nullptr;
     a.epi = EPI_NONE;
     a.acc = 1;
-    int tile = op->tile_override >= 0 ? op->tile_override : choose_tile(a.M, a.Nc, a.nbatch, f64);
+    int tile = op->tile_override >= 0 ? op->tile_override : choose_tile(a.M, a.Nc, a.nbatch, bf3);
     TP3B_HIP(modeprod(op, a, tile, s, bf3));
   }
   return TP3B_OK;
@@ -628,7 +833,7 @@ tp3b_status apply_prec_impl(tp3b_op op, int nvec, const T* X, int64_t ldx, T* Y,
       const T* Xc = X + (int64_t)v0 * ldx;
       T* Yc = Y + (int64_t)v0 * ldy;
       // mode k, factor F (left operand for k < 3, right operand for k = 3)
-      auto pass = [&](int k, const T* F, const T* in, int64_t ldin, T* out, int64_t ldout,
+      auto pass = [&](int k, const T* F, const T* FF, const T* in, int64_t ldin, T* out, int64_t ldout,
                       bool divide) -> tp3b_status {
         ModeProd<T> a{};
         a.X = in; a.ldx = ldin; a.Y = out; a.ldy = ldout;
@@ -639,7 +844,7 @@ tp3b_status apply_prec_impl(tp3b_op op, int nvec, const T* X, int64_t ldx, T* Y,
           default: a.M = n2; a.Nc = n3; a.rs = n3; a.bstride = (int64_t)n2 * n3; a.per_vec = n0 * n1; break;
         }
         a.nbatch = nv * a.per_vec;
-        if (k < 3) a.L = F; else a.R = F;
+        if (k < 3) { a.L = F; a.LF = FF; } else { a.R = F; a.RF = FF; }
         if (divide) {
           a.epi = EPI_DIV;
           a.lamL = d.lam[2];
@@ -647,55 +852,33 @@ tp3b_status apply_prec_impl(tp3b_op op, int nvec, const T* X, int64_t ldx, T* Y,
           a.lamItem = d.lamItem;
           a.sigma = op->sigma;
         }
-        const int tile = op->tile_override >= 0 ? op->tile_override : choose_tile(a.M, a.Nc, a.nbatch, f64);
+        const int tile = op->tile_override >= 0 ? op->tile_override : choose_tile(a.M, a.Nc, a.nbatch, bf3);
         TP3B_HIP(modeprod(op, a, tile, s, bf3));
         return TP3B_OK;
       };
       T* W = d.work;
       tp3b_status st = TP3B_OK;
-      if (st == TP3B_OK) st = pass(0, d.Si[0], Xc, ldx, W, N, false);
-      if (st == TP3B_OK) st = pass(1, d.Si[1], W, N, Yc, ldy, false);
-      if (st == TP3B_OK) st = pass(2, d.Si[2], Yc, ldy, W, N, false);
-      if (st == TP3B_OK) st = pass(3, d.SiT[3], W, N, Yc, ldy, true);
-      if (st == TP3B_OK) st = pass(3, d.ST[3], Yc, ldy, W, N, false);
-      if (st == TP3B_OK) st = pass(2, d.S[2], W, N, Yc, ldy, false);
-      if (st == TP3B_OK) st = pass(1, d.S[1], Yc, ldy, W, N, false);
-      if (st == TP3B_OK) st = pass(0, d.S[0], W, N, Yc, ldy, false);
+      if (st == TP3B_OK) st = pass(0, d.Si[0], d.mSi[0], Xc, ldx, W, N, false);
+      if (st == TP3B_OK) st = pass(1, d.Si[1], d.mSi[1], W, N, Yc, ldy, false);
+      if (st == TP3B_OK) st = pass(2, d.Si[2], d.mSi[2], Yc, ldy, W, N, false);
+      if (st == TP3B_OK) st = pass(3, d.SiT[3], d.mSi[3], W, N, Yc, ldy, true);
+      if (st == TP3B_OK) st = pass(3, d.ST[3], d.mS[3], Yc, ldy, W, N, false);
+      if (st == TP3B_OK) st = pass(2, d.S[2], d.mS[2], W, N, Yc, ldy, false);
+      if (st == TP3B_OK) st = pass(1, d.S[1], d.mS[1], Yc, ldy, W, N, false);
+      if (st == TP3B_OK) st = pass(0, d.S[0], d.mS[0], W, N, Yc, ldy, false);
       if (st != TP3B_OK) return st;
     }
     return TP3B_OK;
   }
-  const int nx = op->n[0], ny = op->n[1];
-  // Z = Sx [ (Sx^{-1} B Sy^{-T}) / (lx_i + ly_j - sigma) ] Sy^T, four mode
-  // products; the work buffer and Y alternate as intermediates.
+  // Z = Sx [ (Sx^{-1} B Sy^{-T}) / (lx_i + ly_j - sigma) ] Sy^T, four mode products
   for (int v0 = 0; v0 < nvec; v0 += op->work_vecs) {
     const int nv = (nvec - v0 < op->work_vecs) ? nvec - v0 : op->work_vecs;
-    const T* Xc = X + (int64_t)v0 * ldx;
-    T* Yc = Y + (int64_t)v0 * ldy;
-    ModeProd<T> a{};
-    a.M = nx;
-    a.Nc = ny;
-    a.rs = ny;
-    a.per_vec = 1;
-    a.nbatch = nv;
-    a.sigma = op->sigma;
-    const int tile = tile_for(op, f64, bf3, 1, nx, ny, nv);
-    // 1: W = Sx^{-1} B
-    a.X = Xc; a.ldx = ldx; a.Y = d.work; a.ldy = N;
-    a.L = d.Si[0]; a.R = nullptr; a.epi = EPI_NONE;
-    TP3B_HIP(modeprod(op, a, tile, s, bf3));
-    // 2: Y = (W Sy^{-T}) / (lx_i + ly_j - sigma)
-    a.X = d.work; a.ldx = N; a.Y = Yc; a.ldy = ldy;
-    a.L = nullptr; a.R = d.SiT[1]; a.epi = EPI_DIV; a.lamL = d.lam[0]; a.lamR = d.lam[1];
-    TP3B_HIP(modeprod(op, a, tile, s, bf3));
-    // 3: W = Sx Y
-    a.X = Yc; a.ldx = ldy; a.Y = d.work; a.ldy = N;
-    a.L = d.S[0]; a.R = nullptr; a.epi = EPI_NONE;
-    TP3B_HIP(modeprod(op, a, tile, s, bf3));
-    // 4: Y = W Sy^T
-    a.X = d.work; a.ldx = N; a.Y = Yc; a.ldy = ldy;
-    a.L = nullptr; a.R = d.ST[1]; a.epi = EPI_NONE;
-    TP3B_HIP(modeprod(op, a, tile, s, bf3));
+    const T* Xv = X + (int64_t)v0 * ldx;
+    T* Yv = Y + (int64_t)v0 * ldy;
+    const bool fold = prec_folded(op, bf3);
+    const int tile = op_tile(op, f64, bf3, 1, nv);
+    for (int st = 0; st < 4; ++st)
+      TP3B_HIP(modeprod(op, prec_job<T>(op, st, nv, Xv, ldx, Yv, ldy, fold), tile, s, bf3));
   }
   return TP3B_OK;
 }
@@ -1097,7 +1280,9 @@ tp3b_status tp3b_create(const tp3b_problem_desc* desc, void* stream, tp3b_op* ou
         pf.S[k].resize((size_t)n * n);
         pf.Si[k].resize((size_t)n * n);
         pf.lam[k].resize(n);
-        ok = eigen_decompose_real(n, Kh[k].data(), pf.S[k].data(), pf.Si[k].data(), pf.lam[k].data());
+        ok = reflection_symmetric(n, Kh[k])
+                 ? parity_decompose(n, Kh[k], pf, k)
+                 : eigen_decompose_real(n, Kh[k].data(), pf.S[k].data(), pf.Si[k].data(), pf.lam[k].data());
       }
       if (ok) {
         // smallest |denominator|: sums over the x modes against sums over the y modes
@@ -1155,6 +1340,7 @@ tp3b_status tp3b_create(const tp3b_problem_desc* desc, void* stream, tp3b_op* ou
       op->y_same_K = Kh[2] == Kh[3];
       op->y_same_S = op->have_prec && pf.S[2] == pf.S[3] && pf.Si[2] == pf.Si[3];
     }
+    op->fold = op->ndim == 1 && reflection_symmetric(op->n[0], Kh[0]) && reflection_symmetric(op->n[1], Kh[1]);
     tp3b_status st = upload_ops<double>(op, op->d64, Kh, pf);
     if (st == TP3B_OK) st = upload_ops<float>(op, op->d32, Kh, pf);
     if (st == TP3B_OK) st = bf3_split_ops(op);
