@@ -282,11 +282,13 @@ namespace tp3b {
 //   P2_SEQ2       Out = (A W) B^T
 //   P2_SEQ2_DIV   Out = [(A W) B^T] / (lamM[m] + lamR[r] + lamC[c] - sigma)
 //   P2_SEQ4_DIV   Out = C ([(A W) A^T] / (lamM[m] + lamR[r] + lamC[c] - sigma)) C^T
-//                 with A = FA1 and C = FA2 (x slabs with equal x modes, FP64)
+//                 with A = FA1 and C = FA2 (equal x modes), or with B^T and D^T,
+//                 B = FB1 and D = FB2, on the right (modes up to P2_SMALL)
 // Matrices that are x slabs (interleaved layout) take P2_SUM, P2_SEQ2 and
 // P2_SEQ4_DIV.
 enum Plane2DProg { P2_SUM = 0, P2_SUM_V_ACC = 1, P2_SEQ2 = 2, P2_SEQ2_DIV = 3, P2_SEQ4_DIV = 4 };
 constexpr int P2_MAXN = 64;
+constexpr int P2_SMALL = 48;  // modes up to this size: k_plane2d_small
 
 template <typename T>
 struct Plane2D {
@@ -302,7 +304,8 @@ struct Plane2D {
   T* Y;
   const T* FA1;     // fragments of A and B (P2_FRAG elements each)
   const T* FB1;
-  const T* FA2;     // P2_SEQ4_DIV: fragments of the second factor (both sides)
+  const T* FA2;     // P2_SEQ4_DIV: fragments of the factors of the way back (with
+  const T* FB2;     // same_ab FB1 and FB2 equal FA1 and FA2 and may be absent)
   int same_ab;      // A and B are the same matrix (equal modes): one LDS copy serves both
   // P2_SUM_V_ACC: the potential from a table in vector layout (V), or, when G is
   // set, from separable Gaussian factors:

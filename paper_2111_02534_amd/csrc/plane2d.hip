@@ -15,7 +15,8 @@
 //                   pass 4 (x slabs): Y = S_x1 W S_x2^T
 // (the mode operators of different modes commute, so the eigenbasis divide by
 // Lambda = lam_x1 + lam_x2 + lam_y1 + lam_y2 - sigma can sit between the y
-// transforms).  HBM traffic is one read and one write per pass (plus the read
+// transforms; modes up to P2_SMALL, and larger equal x modes, also put both x
+// transforms around it, three passes in all).  HBM traffic is one read and one write per pass (plus the read
 // of the x part in the Hamiltonian's second pass), 40 B per entry for the FP64
 // Hamiltonian instead of 72 B for three single-mode passes, 64 B for the
 // preconditioner instead of 128 B for eight.
@@ -30,6 +31,7 @@
 
 #include "device_bodies.h"
 #include "kernels.h"
+#include "modeprod.h"
 
 namespace tp3b {
 
@@ -883,6 +885,265 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
   }
 }
 
+// ------------------------------------------------------------------------
+// Modes up to P2_SMALL: one matrix per wave.
+//
+// A matrix is one to nine MFMA blocks here, and padding it to 64 x 64 (as the
+// kernels above do) was what the time went to: 20 x 20 matrices of 8 FP32
+// vectors took 23 us per pass, 8 % of it products.  Here each wave of a
+// workgroup takes one of G matrices that are neighbours in memory (y planes are
+// one contiguous piece, x slabs G consecutive y indices at every position);
+// together they copy exactly the entries, every load of a thread in flight at
+// once, and from then on a wave has its matrix to itself and meets no barrier.
+// The constant factors come in fragment order from the L2 into registers, a
+// whole factor per wave, K steps past the matrix are not taken, and the
+// preconditioner's slab pass runs both divisions' products at once (three
+// passes over memory instead of five).  Bound by the latency of one round of
+// loads, products and stores up to about 24 (20 x 20: MFMA 21 %, VALU 20 to
+// 29 %), by the copy between memory and LDS beyond.
+// H / P of all modes equal in us, 64 x 64 padded kernel -> this one:
+//   6, 8 vectors    FP64  12.8 / 24.2  ->  11.8 / 14.0
+//   16, 8 vectors   FP64  34.7 / 68.0  ->  11.1 / 20.7   FP32  23.0 / 37.1 -> 10.9 / 16.4
+//   20, 8 vectors   FP64  68.5 / 146   ->  29.9 / 51.3   FP32  49.9 / 90.1 -> 19.7 / 36.4
+//   32, 8 vectors   FP64   201 / 442   ->   113 / 150    FP32   148 / 253  -> 59.4 / 92.0
+//   40, 4 vectors   FP64   239 / 527   ->   188 / 289    FP32   180 / 325  -> 95.1 / 194
+//   48, 4 vectors   FP64   473 / 969   ->   386 / 505    FP32   333 / 550  ->  186 / 311
+// From 56 on it loses (FP64 H 979 -> 1308, FP32 609 -> 642: a factor alone takes
+// half the registers), so the rule's line is at 48, where NB = 3 ends.
+// KS: K steps of four (n <= 4 KS), NB blocks of 16.
+template <typename T, int KS, bool INTERLEAVED>
+struct P2S {
+  static constexpr int NB = (KS + 3) / 4;
+  // matrices per workgroup, one per wave.  FP32 slabs of eight: 32 contiguous
+  // bytes per position instead of 16 (32 modes, H: 91 -> 66 us; FP64 the other
+  // way round, 115 -> 117)
+  static constexpr int G = INTERLEAVED && sizeof(T) == 4 && KS > 4 ? 8 : 4;
+  static constexpr int NT = 64 * G;
+  static constexpr int S = 16 * NB;
+  static constexpr int LD = S + 1, MS = S * LD + 1;  // LDS row and matrix strides
+  static constexpr int ME = (G * 16 * KS * KS + NT - 1) / NT;  // most entries per thread
+};
+
+template <typename T, int KS, int PROG, bool INTERLEAVED>
+__global__ __launch_bounds__((P2S<T, KS, INTERLEAVED>::NT)) __attribute__((amdgpu_waves_per_eu(2)))
+void k_plane2d_small(Plane2D<T> a) {
+  typedef P2S<T, KS, INTERLEAVED> S;
+  typedef typename Mma<T>::acc_t acc_t;
+  constexpr int G = S::G, NB = S::NB, NT = S::NT;
+  __shared__ T w[G * S::MS];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int lr = lane & 15, lk = lane >> 4;
+  const int M = a.M, Nc = a.Nc;
+  const uint32_t groups = (uint32_t)((a.nmat + G - 1) / G);
+  const uint32_t v = blockIdx.x / groups;
+  const int64_t m0 = (int64_t)(blockIdx.x - v * groups) * G;
+  const int nm = (int)min((int64_t)G, a.nmat - m0);  // matrices of this group
+  // Entry e = tid + NT u of the group: of the planes in memory order, of the slabs
+  // position by position with the G y indices of one together.  In both its
+  // place in the vector is the thread's first one plus a uniform step per u, so
+  // the loads are buffer loads from uniform bases (entries past the group read
+  // a neighbour's or zero and are dropped); its place in LDS is walked along with
+  // the carries of row and matrix.  No divisions or products per entry: vector
+  // instructions are what these sizes would otherwise spend their time on.
+  const int count = INTERLEAVED ? G * M * Nc : nm * M * Nc;
+  const int64_t first = (INTERLEAVED ? m0 : m0 * a.js), total = (int64_t)(INTERLEAVED ? M * a.rs : a.nmat * a.js);
+  constexpr int SP = INTERLEAVED ? NT / G : NT;  // positions per step
+  const uint32_t step = (uint32_t)((INTERLEAVED ? SP * a.cs : NT) * sizeof(T));
+  const int p0 = INTERLEAVED ? tid / G : tid, j0 = INTERLEAVED ? tid % G : tid / (M * Nc);
+  const int q0 = INTERLEAVED ? p0 : p0 - j0 * (M * Nc);
+  const uint32_t off0 = (uint32_t)((INTERLEAVED ? j0 + p0 * a.cs : tid) * sizeof(T));
+  const bool mine = !INTERLEAVED || j0 < nm;
+  const int dj = INTERLEAVED ? 0 : SP / (M * Nc), dp = SP - dj * (M * Nc), dr = dp / Nc, dc = dp - dr * Nc;
+  int idx[S::ME];  // places in LDS
+  {
+    int r = q0 / Nc, c = q0 - r * Nc, at = j0 * S::MS + r * S::LD + c;
+#pragma unroll
+    for (int u = 0; u < S::ME; ++u) {
+      idx[u] = at;
+      at += dj * S::MS + dr * S::LD + dc;
+      c += dc;
+      r += dr;
+      if (c >= Nc) {
+        c -= Nc;
+        at += S::LD - Nc;
+        ++r;
+      }
+      if (!INTERLEAVED && r >= M) {
+        r -= M;
+        at += S::MS - M * S::LD;
+      }
+    }
+  }
+  auto buffer = [&](const T* x) {
+    return mp_buffer((const char*)mp_uniform((int64_t)(x + first)), (total - first) * (int64_t)sizeof(T));
+  };
+  const T* X = a.X + v * a.ldx;
+  T* Y = a.Y + v * a.ldy;
+  const __amdgpu_buffer_rsrc_t bx = buffer(X), by = buffer(Y), bv = buffer(a.V ? a.V : X);
+
+  // every load in flight first
+  constexpr bool ACC = PROG == P2_SUM_V_ACC;
+  T raw[S::ME];
+#pragma unroll
+  for (int u = 0; u < S::ME; ++u)
+    if (u * NT < count) raw[u] = mp_load<T>(bx, off0 + u * step);
+  // the first left factor, and zeros in LDS (the padding of the MFMA blocks)
+  T f[NB][KS];
+  auto factor = [&](const T* F) {
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int k = 0; k < KS; ++k) f[b][k] = F[(b * 16 + k) * 64 + lane];
+  };
+  factor(a.FA1);
+  for (int e = tid; e < G * S::MS; e += NT) w[e] = T(0);
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < S::ME; ++u)
+    if (u * NT < count && mine && tid + u * NT < count) w[idx[u]] = raw[u];
+  __syncthreads();
+
+  acc_t acc[NB][NB];
+  auto clear = [&]() {
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+      for (int b = 0; b < NB; ++b) acc[i][b] = acc_t{0, 0, 0, 0};
+  };
+  T* mat = w + wave * S::MS;  // this wave's matrix
+  auto left = [&]() {  // acc += F W
+#pragma unroll
+    for (int k = 0; k < KS; ++k)
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        const T x = mat[(4 * k + lk) * S::LD + b * 16 + lr];
+#pragma unroll
+        for (int i = 0; i < NB; ++i) acc[i][b] = Mma<T>::mma(f[i][k], x, acc[i][b]);
+      }
+  };
+  auto right = [&]() {  // acc += W F^T
+#pragma unroll
+    for (int k = 0; k < KS; ++k)
+#pragma unroll
+      for (int i = 0; i < NB; ++i) {
+        const T x = mat[(i * 16 + lr) * S::LD + 4 * k + lk];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) acc[i][b] = Mma<T>::mma(x, f[b][k], acc[i][b]);
+      }
+  };
+  // a wave's matrix is its own until the group is stored: its LDS accesses are
+  // in order, only the compiler has to keep them so
+  auto own_order = [&]() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
+  // the accumulators into the matrix's place (entries that exist; the padding
+  // stays zero)
+  auto write = [&]() {
+    own_order();
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+      for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int r = i * 16 + Mma<T>::row(lk, q), c = b * 16 + lr;
+          if (r < M && c < Nc) mat[r * S::LD + c] = acc[i][b][q];
+        }
+    own_order();
+  };
+  auto divide = [&]() {
+    const T lm = a.lamM[min(m0 + wave, a.nmat - 1)] - T(a.sigma);
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      const T lc = a.lamC[min(b * 16 + lr, Nc - 1)];
+#pragma unroll
+      for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          acc[i][b][q] = acc[i][b][q] / (lm + a.lamR[min(i * 16 + Mma<T>::row(lk, q), M - 1)] + lc);
+    }
+  };
+
+  clear();
+  left();
+  factor(a.FB1);
+  if (PROG == P2_SUM || ACC) {
+    right();
+  } else {
+    write();
+    clear();
+    right();
+    if (PROG == P2_SEQ4_DIV) {
+      divide();
+      factor(a.FA2);
+      write();
+      clear();
+      left();
+      factor(a.FB2);
+      write();
+      clear();
+      right();
+    }
+  }
+  char* yb = (char*)(Y + first);
+  if constexpr (ACC) {
+    // from the accumulators, a row of blocks at a time: the entries of X are still
+    // in LDS, and nothing but the factors is held in registers during the products
+    if (wave >= nm) return;
+    const T shift = T(a.shifts ? a.shifts[v] : 0.0);
+    const uint32_t lane0 = (uint32_t)((wave * M * Nc + Mma<T>::row(lk, 0) * Nc + lr) * sizeof(T));
+    const uint32_t nq = (uint32_t)((Mma<T>::row(0, 1) - Mma<T>::row(0, 0)) * Nc * sizeof(T));
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      T o[NB][4], p[NB][4];
+      const uint32_t at = lane0 + (uint32_t)(i * 16 * Nc * sizeof(T));
+#pragma unroll
+      for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const uint32_t e = at + q * nq + (uint32_t)(b * 16 * sizeof(T));
+          o[b][q] = mp_load<T>(by, e);
+          p[b][q] = mp_load<T>(bv, e);
+        }
+#pragma unroll
+      for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int r = i * 16 + Mma<T>::row(lk, q), c = b * 16 + lr;
+          const T x = o[b][q] + ((a.V ? p[b][q] : T(0)) - shift) * mat[r * S::LD + c];
+          if (r < M && c < Nc) *(T*)(yb + (at + q * nq + (uint32_t)(b * 16 * sizeof(T)))) = acc[i][b][q] + x;
+        }
+    }
+    return;
+  }
+  write();
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < S::ME; ++u) {
+    if (u * NT < count && mine && tid + u * NT < count) *(T*)(yb + (off0 + u * step)) = w[idx[u]];
+  }
+}
+
+template <typename T, int KS, int PROG, bool INTERLEAVED>
+static hipError_t launch_p2_small(const Plane2D<T>& a, hipStream_t s) {
+  typedef P2S<T, KS, INTERLEAVED> S;
+  const int64_t items = (a.nmat + S::G - 1) / S::G * a.nvec;
+  if (items >= (int64_t)1 << 31) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((k_plane2d_small<T, KS, PROG, INTERLEAVED>), dim3((unsigned)items), dim3(S::NT), 0, s, a);
+  return hipGetLastError();
+}
+
+template <typename T, int KS>
+static hipError_t launch_p2_small(const Plane2D<T>& a, hipStream_t s) {
+  switch (a.prog) {
+    case P2_SUM: return launch_p2_small<T, KS, P2_SUM, true>(a, s);
+    case P2_SUM_V_ACC: return launch_p2_small<T, KS, P2_SUM_V_ACC, false>(a, s);
+    case P2_SEQ2: return launch_p2_small<T, KS, P2_SEQ2, false>(a, s);
+    default: return launch_p2_small<T, KS, P2_SEQ4_DIV, true>(a, s);
+  }
+}
+
 // Two workgroups per CU.
 constexpr int P2Y_GRID = 512;
 
@@ -910,6 +1171,24 @@ hipError_t launch_plane2d(const Plane2D<T>& a, hipStream_t s) {
   if ((a.prog == P2_SEQ2_DIV || a.prog == P2_SEQ4_DIV) && (!a.lamM || !a.lamR || !a.lamC))
     return hipErrorInvalidValue;
   if (a.prog == P2_SEQ4_DIV && !a.FA2) return hipErrorInvalidValue;
+  if (a.prog == P2_SEQ4_DIV && !a.same_ab && (a.M > P2_SMALL || a.Nc > P2_SMALL || !a.FB2))
+    return hipErrorInvalidValue;
+  // small modes (the planes of a group lie one behind the other); the programs
+  // that the applies run on them
+  if (a.M <= P2_SMALL && a.Nc <= P2_SMALL &&
+      (a.interleaved ? a.rs == a.cs * a.Nc && (a.prog == P2_SUM || (a.prog == P2_SEQ4_DIV && a.FB2))
+                     : a.rs == a.Nc && a.js == (int64_t)a.M * a.Nc && (a.prog == P2_SUM_V_ACC || a.prog == P2_SEQ2))) {
+    const int n = a.M > a.Nc ? a.M : a.Nc;
+    if (n <= 8) return launch_p2_small<T, 2>(a, s);
+    if (n <= 12) return launch_p2_small<T, 3>(a, s);
+    if (n <= 16) return launch_p2_small<T, 4>(a, s);
+    if (n <= 20) return launch_p2_small<T, 5>(a, s);
+    if (n <= 24) return launch_p2_small<T, 6>(a, s);
+    if (n <= 28) return launch_p2_small<T, 7>(a, s);
+    if (n <= 32) return launch_p2_small<T, 8>(a, s);
+    if (n <= 40) return launch_p2_small<T, 10>(a, s);
+    return launch_p2_small<T, 12>(a, s);
+  }
   constexpr int J = P2Shape<T>::J;
   const int64_t groups = (a.nmat + J - 1) / J;
   const int64_t items = groups * a.nvec;

@@ -764,13 +764,15 @@ tp3b_status apply_prec_impl(tp3b_op op, int nvec, const T* X, int64_t ldx, T* Y,
       p.X = Xv; p.Y = Yv;
       p.FA1 = d.frSi[0]; p.FB1 = d.frSi[1];
       p.same_ab = op->x_same_S;
-      // equal x modes (FP64: both 64 wide, the y groups in fours and 16-byte
-      // aligned vectors, for the four-matrix kernel)
+      // x modes of the one-matrix-per-wave kernel, or equal ones (FP64: both 64
+      // wide, the y groups in fours and 16-byte aligned vectors, for the
+      // four-matrix kernel)
       const bool seq4 =
-          op->x_same_S &&
+          nx1 <= tp3b::P2_SMALL ||
+          (op->x_same_S &&
           (sizeof(T) == 4 ||
            (nx1 == tp3b::P2_MAXN && nx2 == tp3b::P2_MAXN && Ny % 4 == 0 && ldx % 2 == 0 &&
-            ldy % 2 == 0 && (uintptr_t)X % 16 == 0 && (uintptr_t)Y % 16 == 0));
+            ldy % 2 == 0 && (uintptr_t)X % 16 == 0 && (uintptr_t)Y % 16 == 0)));
       if (seq4) {
         // the two x-slab transforms and the divide in one pass between the two
         // y-plane transforms (the mode transforms commute), so the strided x
@@ -790,7 +792,7 @@ tp3b_status apply_prec_impl(tp3b_op op, int nvec, const T* X, int64_t ldx, T* Y,
         TP3B_HIP(tp3b::launch_plane2d(q, s));
         p.prog = tp3b::P2_SEQ4_DIV;
         p.X = Yv; p.ldx = ldy;
-        p.FA2 = d.frS[0];
+        p.FA2 = d.frS[0]; p.FB2 = d.frS[1];
         p.lamM = d.lamItemY; p.lamR = d.lam[0]; p.lamC = d.lam[1];
         p.sigma = op->sigma;
         TP3B_HIP(tp3b::launch_plane2d(p, s));
@@ -1280,7 +1282,7 @@ tp3b_status tp3b_create(const tp3b_problem_desc* desc, void* stream, tp3b_op* ou
         pf.S[k].resize((size_t)n * n);
         pf.Si[k].resize((size_t)n * n);
         pf.lam[k].resize(n);
-        ok = reflection_symmetric(n, Kh[k])
+        ok = desc->ndim == 1 && reflection_symmetric(n, Kh[k])
                  ? parity_decompose(n, Kh[k], pf, k)
                  : eigen_decompose_real(n, Kh[k].data(), pf.S[k].data(), pf.Si[k].data(), pf.lam[k].data());
       }
