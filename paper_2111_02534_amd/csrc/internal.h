@@ -41,7 +41,8 @@ struct DevOps {
   T* work = nullptr;  // preconditioner intermediate, work_vecs vectors
   // 2D operators with every mode size <= P2_MAXN: MFMA fragments (plane2d.hip)
   // of K_k, S_k and S_k^{-1} per mode, and the separable factors of a Gaussian
-  // potential (4 x 64 x 64, NULL for other potentials).
+  // potential (4 x 64 x 64, NULL for other potentials).  frS and frSi also for 1D
+  // operators of modes up to P1_SMALL.
   T* frK[4] = {nullptr, nullptr, nullptr, nullptr};
   T* frS[4] = {nullptr, nullptr, nullptr, nullptr};
   T* frSi[4] = {nullptr, nullptr, nullptr, nullptr};

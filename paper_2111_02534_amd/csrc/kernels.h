@@ -331,6 +331,25 @@ void plane2d_fragments(int n, const double* A_rowmajor, double* frag_out);
 template <typename T>
 hipError_t launch_plane2d(const Plane2D<T>& a, hipStream_t s);
 
+// A two-mode preconditioner apply in one launch, one workgroup per vector (modes
+// up to P1_SMALL): Y = S_x [(S_x^{-1} X S_y^{-T}) / (lamL[i] + lamR[j] - sigma)] S_y^T
+// with the factors as plane2d_fragments.
+constexpr int P1_SMALL = 64;
+template <typename T>
+struct Prec1D {
+  int M, Nc, nvec;
+  const T* X;
+  T* Y;
+  int64_t ldx, ldy;
+  const T* FSi[2];
+  const T* FS[2];
+  const T* lamL;
+  const T* lamR;
+  double sigma;
+};
+template <typename T>
+hipError_t launch_prec1d(const Prec1D<T>& a, hipStream_t s);
+
 }  // namespace tp3b
 
 namespace tp3b {

@@ -414,11 +414,14 @@ static tp3b_status upload_ops(tp3b_op op, tp3b::DevOps<T>& d, const std::vector<
       TP3B_HIP(upload(&d.fLam[k], lam));
     }
   }
-  if (op->plane2d) {
-    std::vector<double> F(tp3b::P2_FRAG);
+  const bool prec1d = op->ndim == 1 && op->have_prec && std::max(op->n[0], op->n[1]) <= tp3b::P1_SMALL;
+  if (op->plane2d || prec1d) {
+    F.resize(tp3b::P2_FRAG);
     for (int k = 0; k < op->nmodes; ++k) {
-      tp3b::plane2d_fragments(op->n[k], Kh[k].data(), F.data());
-      TP3B_HIP(upload(&d.frK[k], F));
+      if (op->plane2d) {
+        tp3b::plane2d_fragments(op->n[k], Kh[k].data(), F.data());
+        TP3B_HIP(upload(&d.frK[k], F));
+      }
       if (op->have_prec) {
         tp3b::plane2d_fragments(op->n[k], pf.S[k].data(), F.data());
         TP3B_HIP(upload(&d.frS[k], F));
@@ -872,7 +875,21 @@ tp3b_status apply_prec_impl(tp3b_op op, int nvec, const T* X, int64_t ldx, T* Y,
     }
     return TP3B_OK;
   }
-  // Z = Sx [ (Sx^{-1} B Sy^{-T}) / (lx_i + ly_j - sigma) ] Sy^T, four mode products
+  // Z = Sx [ (Sx^{-1} B Sy^{-T}) / (lx_i + ly_j - sigma) ] Sy^T: one launch on small
+  // grids (unless a product's tile is asked for), four mode products otherwise
+  if (d.frSi[0] && !bf3 && op->tile_override < 0) {
+    tp3b::Prec1D<T> a{};
+    a.M = op->n[0]; a.Nc = op->n[1]; a.nvec = nvec;
+    a.X = X; a.Y = Y; a.ldx = ldx; a.ldy = ldy;
+    for (int k = 0; k < 2; ++k) {
+      a.FSi[k] = d.frSi[k];
+      a.FS[k] = d.frS[k];
+    }
+    a.lamL = d.lam[0]; a.lamR = d.lam[1];
+    a.sigma = op->sigma;
+    TP3B_HIP(tp3b::launch_prec1d(a, s));
+    return TP3B_OK;
+  }
   for (int v0 = 0; v0 < nvec; v0 += op->work_vecs) {
     const int nv = (nvec - v0 < op->work_vecs) ? nvec - v0 : op->work_vecs;
     const T* Xv = X + (int64_t)v0 * ldx;
