@@ -253,6 +253,17 @@ hipError_t launch_chol_small(int nx, const double* G, const double* norm0sq, dou
                              double* R, int* flags, hipStream_t s, const int* skip = nullptr);
 // n0[j] = G[j + j nx] for j < nx (the diagonal of a Gram matrix); flag[0] = 1 if
 // any of them is not finite, 0 otherwise.  Single thread.
+// Long blocks (the fits rules): C = Q^T X (nq x nx) and Gram = X^T X (nx x nx) in one
+// pass; the Gram matrix of X R^{-1}, X as it is; X <- (X R^{-1}) R2^{-1}.
+// `partial` as for launch_dot_tn of the larger of the two dots (the Gram).
+bool dot_norms_long_fits(int64_t N, int nq, int nx, const double* Q, int64_t ldq, const double* X, int64_t ldx);
+hipError_t launch_dot_norms_long(int64_t N, int nq, int nx, const double* Q, int64_t ldq, const double* X,
+                                 int64_t ldx, double* C, double* Gram, double* partial, hipStream_t s);
+bool trsm_long_fits(int64_t N, int nx);
+hipError_t launch_trsm_gram(int64_t N, int nx, const double* R, const double* X, int64_t ldx, double* G,
+                            double* partial, hipStream_t s);
+hipError_t launch_trsm_two(int64_t N, int nx, const double* R, const double* R2, double* X, int64_t ldx,
+                           hipStream_t s);
 hipError_t launch_gram_diag(int nx, const double* G, double* n0, int* flag, hipStream_t s);
 // X (N x nx) <- X R^{-1} for upper-triangular R (column-major nx x nx).
 hipError_t launch_trsm_right(int64_t N, int nx, const double* R, double* X, int64_t ldx,

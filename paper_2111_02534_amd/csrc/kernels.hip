@@ -343,31 +343,48 @@ __global__ __launch_bounds__(256) void k_dot_long(int64_t N, int p, int q, const
 // which for many long columns (their starts a large power of two apart)
 // keeps the memory system well below its streaming rate; here each thread
 // instead loads two consecutive rows of one column, so a wave's instruction
-// reads 256 contiguous bytes of each of four columns, and the products take
-// their operands from LDS.  A workgroup takes the 32-row steps b, b + G,
-// b + 2G, ... (G workgroups), the next step's loads in flight while the
-// current one is multiplied; two waves multiply (16 rows each), the four
-// waves' tiles are summed in LDS in wave order as in the block dot.  Padding
+// reads 512 contiguous bytes of each of two columns, and the products take
+// their operands from LDS.  A workgroup takes the 64-row steps b, b + G,
+// b + 2G, ... (G workgroups, as many as are resident at once), the next step's
+// loads in flight while the current one is multiplied; each wave multiplies 16
+// rows, the four waves' tiles are summed in LDS (in the staging buffer) in wave
+// order as in the block dot.  Steps of 32 rows that two waves multiplied, with a
+// buffer of its own for the sum and 2048 workgroups of which 1536 were resident,
+// took longer: 40 columns against 8, N = 2^22, 355 us, and 90 us for the norms of
+// the eight in a pass of their own; both together now 330 us (4.9 TB/s, what a
+// copy reaches).  The last `self` columns of A may be those of B itself (their norms come with a dot that reads
+// B anyway).  Padding
 // columns load column 0 of their operand (their LDS entries feed only
 // outputs outside p x q, which are not stored).  Requires aligned pairs of
 // rows: even leading dimensions and base pointers aligned to two elements.
-constexpr int DOTS_RS = 32;
+// rows of a step; wide tiles take half, or a CU would hold two workgroups
+constexpr int dots_rs(int nc) { return nc <= 96 ? 64 : 32; }
+// row stride of the staged rows: odd, so that the rows a wave stores at once fall
+// on different banks, as do the two lane groups of a half-wave's operand read
+// (rows dots_rs / 4 apart)
+constexpr int dots_ld(int nc) { return nc + 1; }
+// workgroups per CU (= wavefronts per SIMD): by LDS (`more` bytes besides the
+// staged rows), five at most, and two where `blocks` accumulator blocks fill
+// the registers; the grid is what the chip holds at once
+constexpr int dots_wg(int nc, int blocks, int more) {
+  return blocks >= 8 ? 2 : std::min(5, 160 * 1024 / (dots_rs(nc) * dots_ld(nc) * 8 + more));
+}
+constexpr int dots_wg_dot(int pi, int qj) { return dots_wg(16 * (pi + qj), pi * qj, 0); }
+constexpr int dots_wg_gemm(int pq) { return dots_wg(16 * (pq + 1), pq, 2048 * pq); }
 
 template <typename T, int PI, int QJ>
-__global__ __launch_bounds__(256) void k_dot_lds(int64_t N, int p, int q, const T* __restrict__ A,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(dots_wg_dot(PI, QJ))))
+void k_dot_lds(int64_t N, int p, int q, const T* __restrict__ A,
                                                  int64_t lda, const T* __restrict__ B, int64_t ldb,
-                                                 double* __restrict__ part) {
-  constexpr int RS = DOTS_RS;
+                                                 int self, double* __restrict__ part) {
   constexpr int TP = 16 * PI, TQ = 16 * QJ, NC = TP + TQ;
-  // row stride of the staged tile: NC + 4 doubles puts the two lane groups
-  // of a half-wave operand read on disjoint bank halves
-  constexpr int LDW = NC + 4;
+  constexpr int RS = dots_rs(NC), LDW = dots_ld(NC);
   constexpr int SEG = RS / 2;        // threads per column (two rows each)
   constexpr int CPR = 256 / SEG;     // columns per load round
   constexpr int NR = NC / CPR;       // load rounds (NC is a multiple of 16)
   typedef typename std::conditional<std::is_same<T, double>::value, double2, float2>::type T2;
   __shared__ double sm[RS * LDW];
-  __shared__ double red[TP * TQ];
+  static_assert(TP * TQ <= RS * LDW, "the tiles are summed in the staging buffer");
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int lr = lane & 15, lk = lane >> 4;
   const int rp = 2 * (tid % SEG);  // first of this thread's two rows in a step
@@ -379,7 +396,8 @@ __global__ __launch_bounds__(256) void k_dot_lds(int64_t N, int p, int q, const 
     const int c = k * CPR + tid / SEG;
     const bool val = c < TP ? c < p : c - TP < q;
     const int cc = val ? (c < TP ? c : c - TP) : 0;
-    src[k] = (c < TP ? A + (int64_t)cc * lda : B + (int64_t)cc * ldb) + rp;
+    const int cb = c < TP ? cc - (p - self) : cc;  // a column of B
+    src[k] = (c < TP && cb < 0 ? A + (int64_t)cc * lda : B + (int64_t)cb * ldb) + rp;
   }
   const int scol = tid / SEG;  // this thread's column in round 0
   d4 acc[PI][QJ];
@@ -396,21 +414,19 @@ __global__ __launch_bounds__(256) void k_dot_lds(int64_t N, int p, int q, const 
     }
   };
   auto mul = [&]() {
-    if (wave < RS / 16) {
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int r = wave * 16 + 4 * lk + u;
-        double a[PI], bb[QJ];
+    for (int u = 0; u < RS / 16; ++u) {
+      const int r = RS / 4 * lk + RS / 16 * wave + u;
+      double a[PI], bb[QJ];
 #pragma unroll
-        for (int i = 0; i < PI; ++i) a[i] = sm[r * LDW + i * 16 + lr];
+      for (int i = 0; i < PI; ++i) a[i] = sm[r * LDW + i * 16 + lr];
 #pragma unroll
-        for (int j = 0; j < QJ; ++j) bb[j] = sm[r * LDW + TP + j * 16 + lr];
+      for (int j = 0; j < QJ; ++j) bb[j] = sm[r * LDW + TP + j * 16 + lr];
 #pragma unroll
-        for (int i = 0; i < PI; ++i)
+      for (int i = 0; i < PI; ++i)
 #pragma unroll
-          for (int j = 0; j < QJ; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], bb[j], acc[i][j], 0, 0, 0);
-      }
+        for (int j = 0; j < QJ; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], bb[j], acc[i][j], 0, 0, 0);
     }
   };
   // whole steps: workgroup b takes b, b + G, ...; the next step's loads are
@@ -446,6 +462,8 @@ __global__ __launch_bounds__(256) void k_dot_lds(int64_t N, int p, int q, const 
     __syncthreads();
     mul();
   }
+  double* red = sm;
+  __syncthreads();
   for (int wv = 0; wv < 4; ++wv) {
     if (wave == wv) {
 #pragma unroll
@@ -465,28 +483,44 @@ __global__ __launch_bounds__(256) void k_dot_lds(int64_t N, int p, int q, const 
     if (e % TP < p && e / TP < q) out[e] = red[e];
 }
 
-// Sums the chunk partials of k_dot_long: one wavefront per element (p, q),
-// lanes stride over the chunks, then a fixed-order shuffle reduction.  Stores
-// C[i + j ldc] = sum, or C[j + i ldc] with `trans`.
-__global__ __launch_bounds__(256) void k_dot_long_reduce(int p, int q, int tp, int nchunk,
-                                                         const double* __restrict__ part,
-                                                         double* __restrict__ C, int ldc,
-                                                         int trans) {
-  const int lane = threadIdx.x & 63;
-  const int e = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (e >= p * q) return;
-  const int i = e % p, j = e / p;
-  const double* src = part + (int64_t)j * tp + i;
+// Sums the chunk partials of k_dot_long: a workgroup takes eight neighbouring
+// elements of the tile (64 bytes of every chunk's partial), 128 threads each,
+// which stride over the chunks and are summed in LDS in a fixed order.  Stores
+// C[i + j ldc] = sum, or C[j + i ldc] with `trans`; rows i >= p1 go to
+// C2[(i - p1) + j (p - p1)].  (One wavefront per element read 8 bytes of each
+// partial: 40 x 8 over 2048 partials took 20.5 us,
+// over the 1024 there are now 6.7 us.)
+__global__ __launch_bounds__(1024) void k_dot_long_reduce(int p, int q, int tp, int nchunk,
+                                                          const double* __restrict__ part,
+                                                          double* __restrict__ C, int ldc, int trans,
+                                                          int p1, double* __restrict__ C2) {
+  __shared__ double sm[1024];
+  const int tid = threadIdx.x, e = blockIdx.x * 8 + (tid & 7), i = e % tp, j = e / tp;
   const int64_t cs = (int64_t)tp * ((q + 15) / 16) * 16;
   double s = 0.0;
-  for (int c = lane; c < nchunk; c += 64) s += src[(int64_t)c * cs];
-  for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
-  if (lane == 0) {
-    if (trans)
-      C[j + (int64_t)i * ldc] = s;
-    else
-      C[i + (int64_t)j * ldc] = s;
+  if (i < p && j < q) {
+    const double* src = part + e;
+#pragma unroll 4
+    for (int c = tid >> 3; c < nchunk; c += 128) s += src[c * cs];
   }
+  sm[tid] = s;
+  for (int h = 512; h >= 8; h >>= 1) {
+    __syncthreads();
+    if (tid < h) sm[tid] += sm[tid + h];
+  }
+  if (tid < 8 && i < p && j < q) {
+    if (i >= p1)
+      C2[(i - p1) + (int64_t)j * (p - p1)] = sm[tid];
+    else if (trans)
+      C[j + (int64_t)i * ldc] = sm[tid];
+    else
+      C[i + (int64_t)j * ldc] = sm[tid];
+  }
+}
+static void launch_dot_long_reduce(int p, int q, int tp, int nchunk, const double* part, double* C, int ldc,
+                                   int trans, hipStream_t s, int p1 = INT32_MAX, double* C2 = nullptr) {
+  hipLaunchKernelGGL(k_dot_long_reduce, dim3((unsigned)(tp * q / 8)), dim3(1024), 0, s, p, q, tp, nchunk, part,
+                     C, ldc, trans, p1, C2);
 }
 
 template <typename TA, typename TB, int PI, int QJ>
@@ -499,11 +533,10 @@ static int launch_dot_long_pq(int64_t N, int p, int q, const TA* A, int64_t lda,
     // there on the direct loads fall well below the staged ones)
     const bool al = (p + q >= 40) && (((uintptr_t)A | (uintptr_t)B) % (2 * sizeof(TA)) == 0) &&
                     (lda % 2 == 0) && (ldb % 2 == 0);
-    int64_t G = cap / TPQ;
-    if (G > 2048) G = 2048;
+    const int64_t G = std::min<int64_t>(cap / TPQ, 256 * dots_wg_dot(PI, QJ));
     if (al && G >= 256) {
       hipLaunchKernelGGL((k_dot_lds<TA, PI, QJ>), dim3((unsigned)G), dim3(256), 0, s, N, p, q, A,
-                         lda, B, ldb, partial);
+                         lda, B, ldb, 0, partial);
       return (int)G;
     }
   }
@@ -555,8 +588,7 @@ static bool launch_dot_long(int64_t N, int p, int q, const TA* A, int64_t lda, c
                      : launch_dot_long_q<TA, TB, 2>(pi, N, P, Q, A, lda, B, ldb, rc, nchunk, cap, partial, s);
   }
   if (nparts < 0) return false;
-  hipLaunchKernelGGL(k_dot_long_reduce, dim3((unsigned)((P * Q + 3) / 4)), dim3(256), 0, s, P, Q,
-                     16 * pi, nparts, partial, C, ldc, trans ? 1 : 0);
+  launch_dot_long_reduce(P, Q, 16 * pi, nparts, partial, C, ldc, trans ? 1 : 0, s);
   return true;
 }
 
@@ -566,24 +598,27 @@ static bool launch_dot_long(int64_t N, int p, int q, const TA* A, int64_t lda, c
 // (SELF false: the second Gram-Schmidt pass; the same steps, workgroups and
 // product order as k_dot_lds, so it equals launch_dot_tn on the stored Xout)
 // or Xout^T Xout (SELF true: the Gram matrix of the Cholesky-QR).  Rows are
-// staged through LDS in 32-row steps as in k_dot_lds.  Xin may equal Xout
-// (each row is read before it is written, by the same workgroup).
+// staged through LDS in steps as in k_dot_lds.  Xin may equal Xout
+// (each row is read before it is written, by the same workgroup).  Bound by
+// memory: 40 and 8 columns of 2^22 rows, the first update with its dot 530 -> 422
+// us (4.5 TB/s), the second with the Gram matrix 465 -> 415 us (32-row steps, two waves at
+// work, tiles summed in a buffer of their own -> this one).
 template <int PQ, int QJ, bool SELF>
-__global__ __launch_bounds__(256) void k_gemm_dot_lds(int64_t N, int nq, int nx,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(dots_wg_gemm(PQ))))
+void k_gemm_dot_lds(int64_t N, int nq, int nx,
                                                       const double* __restrict__ Q, int64_t ldq,
                                                       const double* __restrict__ C,
                                                       const double* Xin, double* Xout,
                                                       int64_t ldx, double* __restrict__ part) {
-  constexpr int RS = DOTS_RS;
   constexpr int TP = 16 * PQ, TQ = 16 * QJ, NC = TP + TQ;
-  constexpr int LDW = NC + 4;
+  constexpr int RS = dots_rs(NC), LDW = dots_ld(NC);
   constexpr int SEG = RS / 2, CPR = 256 / SEG, NR = NC / CPR;
   constexpr int DP = SELF ? QJ : PQ;   // 16-column blocks of the dot's first operand
   constexpr int TD = 16 * DP;
   constexpr int AOFF = SELF ? TP : 0;  // where that operand sits in the staged rows
   static_assert(QJ == 1, "the update forms 16 columns per wave");
   __shared__ double sm[RS * LDW];
-  __shared__ double red[TD * TQ];
+  static_assert(RS == 64, "one row block per wave");
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int lr = lane & 15, lk = lane >> 4;
   const int rp = 2 * (tid % SEG);
@@ -609,57 +644,52 @@ __global__ __launch_bounds__(256) void k_gemm_dot_lds(int64_t N, int nq, int nx,
       sm[(rp + 1) * LDW + k * CPR + scol] = v[k].y;
     }
   };
-  // The update of the staged rows on the matrix cores: waves 0 and 1 form
+  // The update of the staged rows on the matrix cores: wave w forms
   // D = Q C for rows 16w .. 16w + 15 (A operand from the staged Q rows, the
-  // B operand C[4kk + lk][lr] held in registers) and replace the staged X by
+  // B operand C[4kk + lk][lr] in LDS, entry kk of each lane) and replaces the staged X by
   // X - D; then every thread copies its share of the updated rows to Xout
-  // (32 consecutive rows of a column per half-wave).
-  double creg[4 * PQ];
-#pragma unroll
-  for (int kk = 0; kk < 4 * PQ; ++kk) {
+  // (64 consecutive rows of a column per wave).
+  __shared__ double cf[4 * PQ * 64];
+  for (int kk = wave; kk < 4 * PQ; kk += 4) {
     const int i = 4 * kk + lk;
-    creg[kk] = (i < nq && lr < nx) ? C[i + (int64_t)lr * nq] : 0.0;
+    cf[kk * 64 + lane] = (i < nq && lr < nx) ? C[i + (int64_t)lr * nq] : 0.0;
   }
   auto update = [&]() {
-    if (wave < RS / 16) {
-      d4 dq = d4{0, 0, 0, 0};
+    d4 dq = d4{0, 0, 0, 0};
 #pragma unroll
-      for (int kk = 0; kk < 4 * PQ; ++kk)
-        dq = __builtin_amdgcn_mfma_f64_16x16x4f64(sm[(wave * 16 + lr) * LDW + 4 * kk + lk], creg[kk],
-                                                  dq, 0, 0, 0);
+    for (int kk = 0; kk < 4 * PQ; ++kk)
+      dq = __builtin_amdgcn_mfma_f64_16x16x4f64(sm[(wave * 16 + lr) * LDW + 4 * kk + lk], cf[kk * 64 + lane],
+                                                dq, 0, 0, 0);
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int row = wave * 16 + Mma<double>::row(lk, r);
-        sm[row * LDW + TP + lr] -= dq[r];
-      }
+    for (int r = 0; r < 4; ++r) {
+      const int row = wave * 16 + Mma<double>::row(lk, r);
+      sm[row * LDW + TP + lr] -= dq[r];
     }
   };
   auto copy_out = [&](int64_t r0) {
-    const int rr = tid & 31;
+    const int rr = tid & 63;
     if (r0 + rr < N) {
 #pragma unroll
-      for (int t = 0; t < TQ / 8; ++t) {
-        const int j = (tid >> 5) + 8 * t;
+      for (int t = 0; t < TQ / 4; ++t) {
+        const int j = (tid >> 6) + 4 * t;
         if (j < nx) Xout[r0 + rr + (int64_t)j * ldx] = sm[rr * LDW + TP + j];
       }
     }
   };
   auto mul = [&]() {
-    if (wave < RS / 16) {
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int r = wave * 16 + 4 * lk + u;
-        double a[DP], bb[QJ];
+    for (int u = 0; u < 4; ++u) {
+      const int r = 16 * lk + 4 * wave + u;
+      double a[DP], bb[QJ];
 #pragma unroll
-        for (int i = 0; i < DP; ++i) a[i] = sm[r * LDW + AOFF + i * 16 + lr];
+      for (int i = 0; i < DP; ++i) a[i] = sm[r * LDW + AOFF + i * 16 + lr];
 #pragma unroll
-        for (int j = 0; j < QJ; ++j) bb[j] = sm[r * LDW + TP + j * 16 + lr];
+      for (int j = 0; j < QJ; ++j) bb[j] = sm[r * LDW + TP + j * 16 + lr];
 #pragma unroll
-        for (int i = 0; i < DP; ++i)
+      for (int i = 0; i < DP; ++i)
 #pragma unroll
-          for (int j = 0; j < QJ; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], bb[j], acc[i][j], 0, 0, 0);
-      }
+        for (int j = 0; j < QJ; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], bb[j], acc[i][j], 0, 0, 0);
     }
   };
   const int64_t nfull = N / RS, G = gridDim.x;
@@ -699,6 +729,8 @@ __global__ __launch_bounds__(256) void k_gemm_dot_lds(int64_t N, int nq, int nx,
     copy_out(r0);
     mul();
   }
+  double* red = sm;
+  __syncthreads();
   for (int wv = 0; wv < 4; ++wv) {
     if (wave == wv) {
 #pragma unroll
@@ -741,8 +773,7 @@ hipError_t launch_gemm_dot_long(int64_t N, int nq, int nx, const double* Q, int6
   const int pq = (nq + 15) / 16;
   const int pd = self ? nx : nq;
   const int td = self ? 16 : 16 * pq;
-  int64_t G = dot_scratch_doubles(N, pd, nx) / (td * 16);
-  if (G > 2048) G = 2048;
+  const int64_t G = std::min<int64_t>(dot_scratch_doubles(N, pd, nx) / (td * 16), 256 * dots_wg_gemm(pq));
   if (G < 256) return hipErrorInvalidValue;
   const unsigned g = (unsigned)G;
   switch (pq) {
@@ -757,8 +788,37 @@ hipError_t launch_gemm_dot_long(int64_t N, int nq, int nx, const double* Q, int6
     default: self ? launch_gemm_dot_pq<5, true>(g, N, nq, nx, Q, ldq, C, Xin, Xout, ldx, partial, s)
                   : launch_gemm_dot_pq<5, false>(g, N, nq, nx, Q, ldq, C, Xin, Xout, ldx, partial, s); break;
   }
-  hipLaunchKernelGGL(k_dot_long_reduce, dim3((unsigned)((pd * nx + 3) / 4)), dim3(256), 0, s, pd, nx,
-                     td, (int)G, partial, D, ldd, 0);
+  launch_dot_long_reduce(pd, nx, td, (int)G, partial, D, ldd, 0, s);
+  return hipGetLastError();
+}
+
+bool dot_norms_long_fits(int64_t N, int nq, int nx, const double* Q, int64_t ldq, const double* X, int64_t ldx) {
+  const int pi = (nq + nx + 15) / 16;
+  return N >= DOTL_N && nq >= 1 && nx >= 1 && nx <= 16 && nq + nx <= 16 * DOTL_PI && nq + 2 * nx >= 40 &&
+         (((uintptr_t)Q | (uintptr_t)X) % 16) == 0 && ldq % 2 == 0 && ldx % 2 == 0 &&
+         dot_scratch_doubles(N, nq > nx ? nq : nx, nx) / (256 * pi) >= 256;
+}
+
+template <int PI>
+static void launch_dot_norms_p(unsigned G, int64_t N, int nq, int nx, const double* Q, int64_t ldq, const double* X,
+                               int64_t ldx, double* partial, hipStream_t s) {
+  hipLaunchKernelGGL((k_dot_lds<double, PI, 1>), dim3(G), dim3(256), 0, s, N, nq + nx, nx, Q, ldq, X, ldx, nx, partial);
+}
+
+hipError_t launch_dot_norms_long(int64_t N, int nq, int nx, const double* Q, int64_t ldq, const double* X,
+                                 int64_t ldx, double* C, double* Gram, double* partial, hipStream_t s) {
+  if (!dot_norms_long_fits(N, nq, nx, Q, ldq, X, ldx)) return hipErrorInvalidValue;
+  const int pi = (nq + nx + 15) / 16;
+  const int64_t G = std::min<int64_t>(dot_scratch_doubles(N, nq > nx ? nq : nx, nx) / (256 * pi), 256 * dots_wg_dot(pi, 1));
+  const unsigned g = (unsigned)G;
+  switch (pi) {
+    case 1: launch_dot_norms_p<1>(g, N, nq, nx, Q, ldq, X, ldx, partial, s); break;
+    case 2: launch_dot_norms_p<2>(g, N, nq, nx, Q, ldq, X, ldx, partial, s); break;
+    case 3: launch_dot_norms_p<3>(g, N, nq, nx, Q, ldq, X, ldx, partial, s); break;
+    case 4: launch_dot_norms_p<4>(g, N, nq, nx, Q, ldq, X, ldx, partial, s); break;
+    default: launch_dot_norms_p<5>(g, N, nq, nx, Q, ldq, X, ldx, partial, s); break;
+  }
+  launch_dot_long_reduce(nq + nx, nx, 16 * pi, (int)G, partial, C, nq, 0, s, nq, Gram);
   return hipGetLastError();
 }
 
@@ -1627,6 +1687,132 @@ hipError_t launch_trsm_right(int64_t N, int nx, const double* R, double* X, int6
   if (nx > TRSM_MAX) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_trsm_right, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, s, N, nx, R, X,
                      ldx);
+  return hipGetLastError();
+}
+
+// The second half of a Cholesky-QR on long blocks without X R^{-1} in memory
+// between its two factorisations: first the Gram matrix of X R^{-1} (each wave
+// solves for 64 rows, lays them in LDS and multiplies them there), then
+// X <- (X R^{-1}) R2^{-1}.  The rows are solved in the order of trsm_block, so X
+// comes out as by two solves.  Bound by memory, 1 read and then 1 read and 1
+// write of X instead of 3 and 2: 8 columns of 2^22 rows 285 -> 192 us.
+template <int NX>
+__device__ __forceinline__ void solve_row(int nx, const double* Rs, double (&x)[NX]) {
+#pragma unroll
+  for (int j = 0; j < NX; ++j)
+    if (j < nx) {
+      double s = x[j];
+#pragma unroll
+      for (int i = 0; i < NX; ++i)
+        if (i < j) s -= x[i] * Rs[i + j * nx];
+      x[j] = s / Rs[j + j * nx];
+    }
+}
+
+template <int NX>
+__global__ __launch_bounds__(256) void k_trsm_gram(int64_t N, int nx, const double* __restrict__ R,
+                                                   const double* __restrict__ X, int64_t ldx,
+                                                   double* __restrict__ part) {
+  constexpr int LD = 17;
+  __shared__ double Rs[NX * NX];
+  __shared__ double sm[4][64 * LD];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int lr = lane & 15, lk = lane >> 4;
+  for (int e = tid; e < nx * nx; e += 256) Rs[e] = R[e];
+  double* w = sm[wave];
+#pragma unroll
+  for (int j = 0; j < 16; ++j) w[lane * LD + j] = 0.0;
+  __syncthreads();
+  const int64_t steps = (N + 255) / 256;
+  d4 acc = d4{0, 0, 0, 0};
+  double next[NX];
+  // past the last row: its own zeros
+  auto load = [&](int64_t st) {
+    const int64_t r = st * 256 + tid;
+    const bool in = r < N;
+#pragma unroll
+    for (int j = 0; j < NX; ++j) next[j] = j < nx && in ? X[r + (int64_t)j * ldx] : 0.0;
+  };
+  int64_t st = blockIdx.x;
+  if (st < steps) load(st);
+  for (; st < steps; st += gridDim.x) {
+    double x[NX];
+#pragma unroll
+    for (int j = 0; j < NX; ++j) x[j] = next[j];
+    if (st + gridDim.x < steps) load(st + gridDim.x);
+    if (st * 256 + tid < N) solve_row<NX>(nx, Rs, x);
+    // the wave's own rows: in order, only the compiler has to keep them so
+#pragma unroll
+    for (int j = 0; j < NX; ++j)
+      if (j < nx) w[lane * LD + j] = x[j];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      const double v = w[(16 * lk + k) * LD + lr];
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(v, v, acc, 0, 0, 0);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  }
+  __syncthreads();
+  double* red = sm[0];
+  for (int wv = 0; wv < 4; ++wv) {
+    if (wave == wv) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int idx = lr * 16 + Mma<double>::row(lk, r);
+        red[idx] = (wv == 0) ? acc[r] : red[idx] + acc[r];
+      }
+    }
+    __syncthreads();
+  }
+  part[(int64_t)blockIdx.x * 256 + tid] = red[tid];
+}
+
+template <int NX>
+__global__ __launch_bounds__(256) void k_trsm_two(int64_t N, int nx, const double* __restrict__ R,
+                                                  const double* __restrict__ R2, double* __restrict__ X,
+                                                  int64_t ldx) {
+  __shared__ double Rs[2][NX * NX];
+  for (int e = threadIdx.x; e < nx * nx; e += 256) {
+    Rs[0][e] = R[e];
+    Rs[1][e] = R2[e];
+  }
+  __syncthreads();
+  const int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (r >= N) return;
+  double x[NX];
+#pragma unroll
+  for (int j = 0; j < NX; ++j) x[j] = j < nx ? X[r + (int64_t)j * ldx] : 0.0;
+  solve_row<NX>(nx, Rs[0], x);
+  solve_row<NX>(nx, Rs[1], x);
+#pragma unroll
+  for (int j = 0; j < NX; ++j)
+    if (j < nx) X[r + (int64_t)j * ldx] = x[j];
+}
+
+bool trsm_long_fits(int64_t N, int nx) {
+  return N >= DOTL_N && nx >= 1 && nx <= 16 && dot_scratch_doubles(N, nx, nx) / 256 >= 256;
+}
+
+hipError_t launch_trsm_gram(int64_t N, int nx, const double* R, const double* X, int64_t ldx, double* G,
+                            double* partial, hipStream_t s) {
+  if (!trsm_long_fits(N, nx)) return hipErrorInvalidValue;
+  // four resident workgroups per CU (35 to 37 KB of LDS each)
+  const int g = (int)std::min<int64_t>(dot_scratch_doubles(N, nx, nx) / 256, 1024);
+  if (nx <= 8) hipLaunchKernelGGL((k_trsm_gram<8>), dim3(g), dim3(256), 0, s, N, nx, R, X, ldx, partial);
+  else hipLaunchKernelGGL((k_trsm_gram<16>), dim3(g), dim3(256), 0, s, N, nx, R, X, ldx, partial);
+  launch_dot_long_reduce(nx, nx, 16, g, partial, G, nx, 0, s);
+  return hipGetLastError();
+}
+
+hipError_t launch_trsm_two(int64_t N, int nx, const double* R, const double* R2, double* X, int64_t ldx,
+                           hipStream_t s) {
+  if (!trsm_long_fits(N, nx)) return hipErrorInvalidValue;
+  const dim3 g((unsigned)((N + 255) / 256));
+  if (nx <= 8) hipLaunchKernelGGL((k_trsm_two<8>), g, dim3(256), 0, s, N, nx, R, R2, X, ldx);
+  else hipLaunchKernelGGL((k_trsm_two<16>), g, dim3(256), 0, s, N, nx, R, R2, X, ldx);
   return hipGetLastError();
 }
 

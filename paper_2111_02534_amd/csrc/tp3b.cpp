@@ -947,12 +947,16 @@ tp3b_status block_orth_queue(int64_t N, int nq, const double* Q, int64_t ldq, in
   int* fl1 = dflags;                        // first Cholesky: dependence flags
   int* nonfin = dflags + nx;                // non-finite input
   // the dependence test reads the input norms on the device
-  TP3B_HIP(launch_dot_tn<double, double>(N, nx, nx, Xin, ldx, Xin, ldx, G, nx, part, s));
+  const bool norms = nq > 0 && dot_norms_long_fits(N, nq, nx, Q, ldq, Xin, ldx);
+  if (norms)
+    TP3B_HIP(launch_dot_norms_long(N, nq, nx, Q, ldq, Xin, ldx, C1, G, part, s));
+  else
+    TP3B_HIP(launch_dot_tn<double, double>(N, nx, nx, Xin, ldx, Xin, ldx, G, nx, part, s));
   TP3B_HIP(launch_gram_diag(nx, G, n0, nonfin, s));
   bool gram_done = false;
   if (nq > 0) {
     // the first pass reads the input and writes X = Xin - Q C1
-    TP3B_HIP(launch_dot_tn<double, double>(N, nq, nx, Q, ldq, Xin, ldx, C1, nq, part, s));
+    if (!norms) TP3B_HIP(launch_dot_tn<double, double>(N, nq, nx, Q, ldq, Xin, ldx, C1, nq, part, s));
     // long blocks: each update also forms the next dot on the rows it has just
     // written (the second pass's coefficients, then the Gram matrix), so Q and
     // X are not read again for them
@@ -968,13 +972,19 @@ tp3b_status block_orth_queue(int64_t N, int nq, const double* Q, int64_t ldq, in
   }
   if (!gram_done) TP3B_HIP(launch_dot_tn<double, double>(N, nx, nx, X, ldx, X, ldx, G, nx, part, s));
   TP3B_HIP(launch_chol_small(nx, G, n0, kDropTol, R1, fl1, s));
-  TP3B_HIP(launch_trsm_right(N, nx, R1, X, ldx, s));
-  TP3B_HIP(launch_dot_tn<double, double>(N, nx, nx, X, ldx, X, ldx, G, nx, part, s));
+  const bool two = trsm_long_fits(N, nx);
+  if (two) {
+    TP3B_HIP(launch_trsm_gram(N, nx, R1, X, ldx, G, part, s));
+  } else {
+    TP3B_HIP(launch_trsm_right(N, nx, R1, X, ldx, s));
+    TP3B_HIP(launch_dot_tn<double, double>(N, nx, nx, X, ldx, X, ldx, G, nx, part, s));
+  }
   // the second factorisation leaves the columns the first found dependent out,
   // so the independent columns keep exactly their span (the flagged ones are
   // replaced by the caller)
   TP3B_HIP(launch_chol_small(nx, G, n0, 0.0, R2, fl2, s, fl1));
-  TP3B_HIP(launch_trsm_right(N, nx, R2, X, ldx, s));
+  if (two) TP3B_HIP(launch_trsm_two(N, nx, R1, R2, X, ldx, s));
+  else TP3B_HIP(launch_trsm_right(N, nx, R2, X, ldx, s));
   return TP3B_OK;
 }
 
