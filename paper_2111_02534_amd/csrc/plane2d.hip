@@ -26,7 +26,8 @@
 // the two modes of a pass have the same operator (equal n and L), one copy
 // serves both products, and two more shapes use the LDS this frees:
 // k_plane2d_x4 (FP64 x slabs, items of four matrices: 32-byte pieces) and
-// k_plane2d_y1 (y planes, one plane per item, two workgroups per CU).
+// k_plane2d_y1 (y planes, one plane per item, two workgroups per CU; its FP64
+// P2_SEQ2 is k_plane2d_seq2, three workgroups with the factor in registers).
 #include <hip/hip_runtime.h>
 
 #include "device_bodies.h"
@@ -886,6 +887,118 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void k
 }
 
 // ------------------------------------------------------------------------
+// FP64 y planes with equal y modes, (F W) F^T: the factor in registers.
+//
+// A workgroup of four waves holds one plane (32 KB, swizzled instead of padded),
+// three workgroups per CU.  Wave b computes rows 16 b .. of F W and then columns
+// 16 b .. of (F W) F^T, so it needs the same sixteen fragments of the one factor
+// for both, and these stay in its registers for all its items: the products read
+// one operand from LDS (five reads per four products in the layout of
+// k_plane2d_y1, whose waves share the factor there), a step ahead, from places
+// that differ by constants, so that almost nothing but matrix instructions
+// is issued in between.  Bound by those: 64^4, passes of four vectors, 307 -> 268 us
+// (matrix cores 75 -> 83 % busy).  The same split for the x slabs took 947 us
+// against 841 us (two matrices per workgroup: 16-byte pieces instead of 32).
+// Requires what k_plane2d_y1 does.
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_plane2d_seq2(Plane2D<double> a) {
+  constexpr int PER = 8;  // 16-byte chunks per thread
+  __shared__ double w[P2_MAXN * P2_MAXN];
+  const int tid = threadIdx.x, lane = tid & 63, b = tid >> 6;
+  const int lr = lane & 15, lk = lane >> 4;
+  const int64_t total = a.nmat * a.nvec, G = gridDim.x;
+
+  // places in LDS: entry (r, c) at 64 r + (c ^ swz(r)); al: rows lk + 4 t of a
+  // block, even and odd column blocks; ar: k steps of half a row
+  int al[4][2], ar[8];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const int r = lk + 4 * t, z = p2x_swz(r, 0);
+    al[t][0] = r * 64 + (lr ^ z);
+    al[t][1] = r * 64 + ((16 + lr) ^ z);
+  }
+#pragma unroll
+  for (int k = 0; k < 8; ++k) ar[k] = lr * 64 + ((4 * k + lk) ^ p2x_swz(lr, 0));
+
+  double f[16];
+#pragma unroll
+  for (int k = 0; k < 16; ++k) f[k] = a.FA1[(b * 16 + k) * 64 + lane];
+
+  double2 pre[PER];
+  auto fetch = [&](int64_t item) {
+    const int64_t v = item / a.nmat, m = item - v * a.nmat;
+    const __amdgpu_buffer_rsrc_t bx =
+        mp_buffer((const char*)mp_uniform((int64_t)(a.X + v * a.ldx + m * a.js)), P2_MAXN * P2_MAXN * 8);
+#pragma unroll
+    for (int u = 0; u < PER; ++u) pre[u] = mp_load<double2>(bx, (uint32_t)tid * 16 + u * 4096);
+  };
+  auto put = [&]() {
+    const int r0 = tid >> 5, c0 = 2 * (tid & 31);
+#pragma unroll
+    for (int u = 0; u < PER; ++u) *(double2*)(w + (r0 + 8 * u) * 64 + (c0 ^ p2x_swz(r0 + 8 * u, 0))) = pre[u];
+  };
+
+  int64_t item = p2_slot(blockIdx.x, (int)G);
+  if (item < total) {
+    fetch(item);
+    put();
+  }
+  __syncthreads();
+  for (; item < total; item += G) {
+    const int64_t nxt = item + G;
+    if (nxt < total) fetch(nxt);
+    d4 acc[4];
+    double x[2][4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) acc[c] = d4{0, 0, 0, 0};
+    // rows 16 b .. of F W, acc[c]: column block c
+    auto read_left = [&](int k) {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) x[k & 1][c] = w[(k >> 2) * 1024 + al[k & 3][c & 1] + (c >> 1) * 32];
+    };
+    read_left(0);
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      if (k < 15) read_left(k + 1);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) acc[c] = Mma<double>::mma(f[k], x[k & 1][c], acc[c]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) w[b * 1024 + al[q][c & 1] + (c >> 1) * 32] = acc[c][q];
+    __syncthreads();
+    // columns 16 b .. of (F W) F^T, acc[i]: row block i
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc[i] = d4{0, 0, 0, 0};
+    auto read_right = [&](int k) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) x[k & 1][i] = w[i * 1024 + ar[k & 7] + (k >> 3) * 32];
+    };
+    read_right(0);
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      if (k < 15) read_right(k + 1);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc[i] = Mma<double>::mma(x[k & 1][i], f[k], acc[i]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    __syncthreads();
+    if (nxt < total) put();
+    const int64_t v = item / a.nmat, m = item - v * a.nmat;
+    double* Y = a.Y + v * a.ldy + m * a.js + lk * 64 + b * 16 + lr;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) Y[(i * 16 + 4 * q) * 64] = acc[i][q];
+    __syncthreads();
+  }
+}
+// Three workgroups per CU.
+constexpr int P2Q_GRID = 768;
+
+// ------------------------------------------------------------------------
 // Modes up to P2_SMALL: one matrix per wave.
 //
 // A matrix is one to nine MFMA blocks here, and padding it to 64 x 64 (as the
@@ -1233,11 +1346,15 @@ hipError_t launch_plane2d(const Plane2D<T>& a, hipStream_t s) {
   if (y1) {
     const int64_t items1 = a.nmat * a.nvec;
     const unsigned grid1 = (unsigned)(items1 < P2Y_GRID ? items1 : P2Y_GRID);
-    if (a.prog == P2_SUM_V_ACC)
+    const unsigned gridq = (unsigned)(items1 < P2Q_GRID ? items1 : P2Q_GRID);
+    if (a.prog == P2_SUM_V_ACC) {
       hipLaunchKernelGGL((k_plane2d_y1<T, P2_SUM_V_ACC>), dim3(grid1), dim3(512), 0, s, b);
-    else if (a.prog == P2_SEQ2)
-      hipLaunchKernelGGL((k_plane2d_y1<T, P2_SEQ2>), dim3(grid1), dim3(512), 0, s, b);
-    else
+    } else if (a.prog == P2_SEQ2) {
+      if constexpr (sizeof(T) == 8)
+        hipLaunchKernelGGL(k_plane2d_seq2, dim3(gridq), dim3(256), 0, s, b);
+      else
+        hipLaunchKernelGGL((k_plane2d_y1<T, P2_SEQ2>), dim3(grid1), dim3(512), 0, s, b);
+    } else
       hipLaunchKernelGGL((k_plane2d_y1<T, P2_SEQ2_DIV>), dim3(grid1), dim3(512), 0, s, b);
     return hipGetLastError();
   }

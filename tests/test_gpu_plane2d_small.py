@@ -72,3 +72,27 @@ def test_small_modes(k, prec):
     assert err <= bars[0] and perr <= bars[1]
     assert (buf[:, :, P.N:] == 7.0).all()
     op.close()
+
+
+@pytest.mark.parametrize("nx,pad", [(3, 0), (5, 2), (28, 0)])
+def test_full_equal_planes_prec(nx, pad):
+    """Full 64 x 64 y planes with equal modes (FP64: the factor in registers), fewer
+    and more planes than workgroups, and a strided block; bar as above."""
+    import torch
+    t3 = need_gpu()
+    n, L = (nx, nx, 64, 64), (5.0, 5.0, 9.0, 9.0)
+    cx, cy, mu = physics.coeffs_unit_heavy(20.0)
+    P = problem.make_problem(ndim=2, n=n, L=L, alpha=20.0, v0=2.5, width=0.9, shape="gauss")
+    op = t3.Operator(2, list(n), list(L), cx, cy, v0=2.5, width=0.9, sigma=P.two_body_shift(), mu_hl=mu)
+    buf = torch.full((2, 2, P.N + pad), 7.0, dtype=torch.float64, device="cuda")
+    X, Y = buf[0, :, :P.N], buf[1, :, :P.N]
+    X.copy_(to_dev(normal_block(P.N, 2, 50 + nx)))
+    say("full equal planes", n)
+    op.apply_prec(X, Y)
+    torch.cuda.synchronize()
+    want = P.preconditioner(sigma=op.sigma).apply(X.cpu().numpy().T).T
+    err = np.linalg.norm(Y.cpu().numpy() - want) / np.linalg.norm(want)
+    say("  P", err)
+    assert err <= 1e-10
+    assert (buf[:, :, P.N:] == 7.0).all()
+    op.close()
