@@ -107,17 +107,22 @@ hipError_t mp_launch(const MpTabs<float>& m, hipStream_t s) {
 }
 
 // The tables of one grouped preconditioner apply: four steps, each as plain and
-// as folded products (an instance has its job in one of the two).
+// as folded products, and the applies of one launch (an instance has its job in
+// one of the three).
 template <typename T>
 struct PrecTabs {
   MpTabs<T> mp[2][4];
   bool use[2] = {false, false};
+  Tab<Prec1D<T>> one;
+  bool use_one = false;
 };
 
 template <typename T>
 bool prec_alloc(TableArena& ar, const tp3b_op* ops, int count, const TileSet& ts, int cap, bool bf3, PrecTabs<T>& p) {
-  for (int i = 0; i < count; ++i) p.use[prec_folded(ops[i], bf3)] = true;
-  bool ok = true;
+  for (int i = 0; i < count; ++i)
+    if (prec_one<T>(ops[i], bf3)) p.use_one = true;
+    else p.use[prec_folded(ops[i], bf3)] = true;
+  bool ok = !p.use_one || ar.alloc(p.one, cap);
   for (int f = 0; f < 2; ++f)
     for (int st = 0; st < 4 && p.use[f]; ++st) {
       ok = ok && mp_alloc(ar, ts, cap, bf3, p.mp[f][st]);
@@ -128,6 +133,10 @@ bool prec_alloc(TableArena& ar, const tp3b_op* ops, int count, const TileSet& ts
 
 template <typename T>
 bool prec_add(PrecTabs<T>& p, tp3b_op op, bool bf3, int nv, const T* X, int64_t ldx, T* Y, int64_t ldy, int tile) {
+  if (prec_one<T>(op, bf3)) {
+    TableArena::add(p.one, prec1d_job<T>(op, nv, X, ldx, Y, ldy), nv);
+    return true;
+  }
   const bool fold = prec_folded(op, bf3);
   for (int st = 0; st < 4; ++st)
     if (!mp_add(p.mp[fold][st], prec_job<T>(op, st, nv, X, ldx, Y, ldy, fold), tile)) return false;
@@ -136,7 +145,7 @@ bool prec_add(PrecTabs<T>& p, tp3b_op op, bool bf3, int nv, const T* X, int64_t 
 
 template <typename T>
 hipError_t prec_launch(const PrecTabs<T>& p, hipStream_t s) {
-  hipError_t e = hipSuccess;
+  hipError_t e = p.use_one ? launch_prec1d_grouped<T>(p.one.d, s) : hipSuccess;
   for (int st = 0; st < 4; ++st)
     for (int f = 0; f < 2 && e == hipSuccess; ++f)
       if (p.use[f]) e = mp_launch(p.mp[f][st], s);

@@ -764,4 +764,82 @@ __device__ __forceinline__ double hash_uniform(uint64_t seed, uint64_t sid, int6
   return (double)(h >> 11) * (2.0 / 9007199254740992.0) - 1.0;
 }
 
+// ------------------------------------------------------------------------
+// Two-mode preconditioner on small grids: the whole apply in one workgroup.
+//
+// Four mode products of up to 64 x 64 matrices are few us of matrix instructions
+// on one CU, but as four launches they cost 4 us each, nearly all of it launch,
+// first access and drain.  Apply of 4 vectors, four launches -> this one: FP64
+// 16 x 16 16.2 -> 8.7 us, 32 x 32 16.5 -> 8.8, 48 x 48 17.6 -> 8.8; FP32 16 x 16
+// 16.6 -> 8.7, 64 x 64 17.6 -> 8.8 (8.5 us is what an apply costs its caller at
+// the least).  FP64 ends at 48 (p1_small): 64 x 64 17.2 -> 14.4, of which 7 are
+// products, and grouped applies, which run the larger instances' products in any
+// case, would get a launch more for it.
+// Here wave (bi, bj) of NB x NB owns one 16 x 16 block of the vector through all four products; the
+// products exchange their operand through two LDS buffers (one barrier per
+// product), and each wave reads the next product's factor while it computes.
+template <int NB>
+struct P1Lds {
+  static constexpr int LD = 16 * NB + 1, SZ = 16 * NB * LD;
+};
+template <typename T, int NB>
+__device__ __forceinline__ void prec1d_vector(const Prec1D<T>& a, int64_t v, T (&w)[2][P1Lds<NB>::SZ]) {
+  typedef typename Mma<T>::acc_t acc_t;
+  constexpr int LD = P1Lds<NB>::LD, KS = 4 * NB;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lr = lane & 15, lk = lane >> 4;
+  const int bi = wave / NB, bj = wave % NB;
+  const int M = a.M, Nc = a.Nc;
+  const T* X = a.X + v * a.ldx;
+  T* Y = a.Y + v * a.ldy;
+  const int c = bj * 16 + lr;
+  int row[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) row[q] = bi * 16 + Mma<T>::row(lk, q);
+
+  acc_t acc;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) acc[q] = row[q] < M && c < Nc ? X[(int64_t)row[q] * Nc + c] : T(0);
+  T f[2][KS];
+  auto factor = [&](int i, const T* F, int b) {
+#pragma unroll
+    for (int k = 0; k < KS; ++k) f[i][k] = F[(b * 16 + k) * 64 + lane];
+  };
+  factor(0, a.FSi[0], bi);
+  T lr4[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) lr4[q] = a.lamL[min(row[q], M - 1)];
+  const T lc = a.lamR[min(c, Nc - 1)];
+  auto put = [&](T* W) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) W[row[q] * LD + c] = acc[q];
+    __syncthreads();
+    acc = acc_t{0, 0, 0, 0};
+  };
+  auto left = [&](const T* W, const T* F) {
+#pragma unroll
+    for (int k = 0; k < KS; ++k) acc = Mma<T>::mma(F[k], W[(4 * k + lk) * LD + c], acc);
+  };
+  auto right = [&](const T* W, const T* F) {
+#pragma unroll
+    for (int k = 0; k < KS; ++k) acc = Mma<T>::mma(W[(bi * 16 + lr) * LD + 4 * k + lk], F[k], acc);
+  };
+  put(w[0]);
+  factor(1, a.FSi[1], bj);
+  left(w[0], f[0]);
+  put(w[1]);
+  factor(0, a.FS[0], bi);
+  right(w[1], f[1]);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) acc[q] = acc[q] / (lr4[q] + lc - T(a.sigma));
+  put(w[0]);
+  factor(1, a.FS[1], bj);
+  left(w[0], f[0]);
+  put(w[1]);
+  right(w[1], f[1]);
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    if (row[q] < M && c < Nc) Y[(int64_t)row[q] * Nc + c] = acc[q];
+}
+
 }  // namespace tp3b

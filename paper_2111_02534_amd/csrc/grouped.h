@@ -196,6 +196,8 @@ class TableArena {
 // with them.
 template <typename T>
 hipError_t launch_modeprod_grouped(DevTab<ModeProd<T>> t, int tile, int mode, hipStream_t s);
+template <typename T>
+hipError_t launch_prec1d_grouped(DevTab<Prec1D<T>> t, hipStream_t s);
 hipError_t launch_modeprod_bf3_grouped(DevTab<ModeProd<float>> t, int tile, hipStream_t s);
 int64_t modeprod_items_for(int M, int Nc, int nbatch, int tile, bool bf3);
 

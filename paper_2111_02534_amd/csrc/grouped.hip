@@ -130,6 +130,23 @@ hipError_t launch_modeprod_bf3_grouped(DevTab<ModeProd<float>> t, int tile, hipS
   return hipGetLastError();
 }
 
+template <typename T, int NB>
+__global__ __launch_bounds__(64 * NB * NB) void k_prec1d_grouped(DevTab<Prec1D<T>> t) {
+  __shared__ T w[2][P1Lds<NB>::SZ];
+  for_wg_items(t, 0, [&](const Prec1D<T>& a, int64_t v) { prec1d_vector<T, NB>(a, v, w); });
+}
+
+// All sizes in blocks of the largest: the steps past a matrix add zeros, so every
+// instance gets the result of its own launch.
+template <typename T>
+hipError_t launch_prec1d_grouped(DevTab<Prec1D<T>> t, hipStream_t s) {
+  constexpr int NB = p1_small<T>() / 16;
+  hipLaunchKernelGGL((k_prec1d_grouped<T, NB>), dim3(kPersistWGs / 4), dim3(64 * NB * NB), 0, s, t);
+  return hipGetLastError();
+}
+template hipError_t launch_prec1d_grouped<double>(DevTab<Prec1D<double>>, hipStream_t);
+template hipError_t launch_prec1d_grouped<float>(DevTab<Prec1D<float>>, hipStream_t);
+
 // ------------------------------------------------------------------- dots
 int64_t dot_job_partials(int64_t N, int p, int q) {
   const int rc = dot_row_chunk_grouped(N);

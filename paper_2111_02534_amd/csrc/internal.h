@@ -42,7 +42,7 @@ struct DevOps {
   // 2D operators with every mode size <= P2_MAXN: MFMA fragments (plane2d.hip)
   // of K_k, S_k and S_k^{-1} per mode, and the separable factors of a Gaussian
   // potential (4 x 64 x 64, NULL for other potentials).  frS and frSi also for 1D
-  // operators of modes up to P1_SMALL.
+  // operators of modes up to p1_small.
   T* frK[4] = {nullptr, nullptr, nullptr, nullptr};
   T* frS[4] = {nullptr, nullptr, nullptr, nullptr};
   T* frSi[4] = {nullptr, nullptr, nullptr, nullptr};
@@ -175,6 +175,12 @@ ModeProd<T> h_job(tp3b_op op, int nvec, const T* X, int64_t ldx, T* Y, int64_t l
 template <typename T>
 ModeProd<T> prec_job(tp3b_op op, int st, int nv, const T* X, int64_t ldx, T* Y, int64_t ldy, bool fold);
 // Whether the preconditioner runs folded (FP64 and FP32).
+// Whether a 1D preconditioner apply runs as one launch (small grids, unless a tile
+// is asked for), and its job.
+template <typename T>
+bool prec_one(tp3b_op op, bool bf3);
+template <typename T>
+tp3b::Prec1D<T> prec1d_job(tp3b_op op, int nvec, const T* X, int64_t ldx, T* Y, int64_t ldy);
 bool prec_folded(tp3b_op op, bool bf3);
 int choose_tile(int M, int Nc, int64_t nbatch, bool bf3);
 // Second-derivative matrix (row-major, desc->D2[k] when given) and ascending

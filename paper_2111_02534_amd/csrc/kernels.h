@@ -343,9 +343,10 @@ template <typename T>
 hipError_t launch_plane2d(const Plane2D<T>& a, hipStream_t s);
 
 // A two-mode preconditioner apply in one launch, one workgroup per vector (modes
-// up to P1_SMALL): Y = S_x [(S_x^{-1} X S_y^{-T}) / (lamL[i] + lamR[j] - sigma)] S_y^T
+// up to p1_small, see prec1d_vector): Y = S_x [(S_x^{-1} X S_y^{-T}) / (lamL[i] + lamR[j] - sigma)] S_y^T
 // with the factors as plane2d_fragments.
-constexpr int P1_SMALL = 64;
+template <typename T>
+constexpr int p1_small() { return sizeof(T) == 8 ? 48 : 64; }
 template <typename T>
 struct Prec1D {
   int M, Nc, nvec;

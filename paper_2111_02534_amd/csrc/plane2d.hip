@@ -1379,91 +1379,22 @@ hipError_t launch_plane2d(const Plane2D<T>& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// ------------------------------------------------------------------------
-// Two-mode preconditioner on small grids: the whole apply in one workgroup.
-//
-// Four mode products of up to 64 x 64 matrices are 7 us of matrix instructions on
-// one CU (48 x 48: 3 us), but as four launches they cost 4 us each, nearly all of
-// it launch, first access and drain.  Apply of 4 vectors, four launches -> this
-// one, FP64 (FP32): 16 x 16 16.2 -> 8.7 us (16.6 -> 8.7), 32 x 32 16.5 -> 8.8
-// (16.6 -> 8.8), 48 x 48 17.6 -> 8.8 (17.4 -> 8.8), 64 x 64 17.2 -> 14.4
-// (17.6 -> 8.8); 8.5 us is what an apply costs its caller at the least.  Past 64
-// one CU's matrix units are the longer way (80 x 80 in FP64: 14 us of products
-// alone).  Here wave (bi, bj) of
-// NB x NB owns one 16 x 16 block of the vector through all four products; the
-// products exchange their operand through two LDS buffers (one barrier per
-// product), and each wave reads the next product's factor while it computes.
 template <typename T, int NB>
 __global__ __launch_bounds__(64 * NB * NB) void k_prec1d(Prec1D<T> a) {
-  typedef typename Mma<T>::acc_t acc_t;
-  constexpr int S = 16 * NB, LD = S + 1, KS = 4 * NB;
-  __shared__ T w[2][S * LD];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int lr = lane & 15, lk = lane >> 4;
-  const int bi = wave / NB, bj = wave % NB;
-  const int M = a.M, Nc = a.Nc;
-  const T* X = a.X + blockIdx.x * a.ldx;
-  T* Y = a.Y + blockIdx.x * a.ldy;
-  const int c = bj * 16 + lr;
-  int row[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) row[q] = bi * 16 + Mma<T>::row(lk, q);
-
-  acc_t acc;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) acc[q] = row[q] < M && c < Nc ? X[(int64_t)row[q] * Nc + c] : T(0);
-  T f[2][KS];
-  auto factor = [&](int i, const T* F, int b) {
-#pragma unroll
-    for (int k = 0; k < KS; ++k) f[i][k] = F[(b * 16 + k) * 64 + lane];
-  };
-  factor(0, a.FSi[0], bi);
-  T lr4[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) lr4[q] = a.lamL[min(row[q], M - 1)];
-  const T lc = a.lamR[min(c, Nc - 1)];
-  auto put = [&](T* W) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) W[row[q] * LD + c] = acc[q];
-    __syncthreads();
-    acc = acc_t{0, 0, 0, 0};
-  };
-  auto left = [&](const T* W, const T* F) {
-#pragma unroll
-    for (int k = 0; k < KS; ++k) acc = Mma<T>::mma(F[k], W[(4 * k + lk) * LD + c], acc);
-  };
-  auto right = [&](const T* W, const T* F) {
-#pragma unroll
-    for (int k = 0; k < KS; ++k) acc = Mma<T>::mma(W[(bi * 16 + lr) * LD + 4 * k + lk], F[k], acc);
-  };
-  put(w[0]);
-  factor(1, a.FSi[1], bj);
-  left(w[0], f[0]);
-  put(w[1]);
-  factor(0, a.FS[0], bi);
-  right(w[1], f[1]);
-#pragma unroll
-  for (int q = 0; q < 4; ++q) acc[q] = acc[q] / (lr4[q] + lc - T(a.sigma));
-  put(w[0]);
-  factor(1, a.FS[1], bj);
-  left(w[0], f[0]);
-  put(w[1]);
-  right(w[1], f[1]);
-#pragma unroll
-  for (int q = 0; q < 4; ++q)
-    if (row[q] < M && c < Nc) Y[(int64_t)row[q] * Nc + c] = acc[q];
+  __shared__ T w[2][P1Lds<NB>::SZ];
+  prec1d_vector<T, NB>(a, blockIdx.x, w);
 }
 
 template <typename T>
 hipError_t launch_prec1d(const Prec1D<T>& a, hipStream_t s) {
   if (a.nvec <= 0) return hipSuccess;
   const int n = a.M > a.Nc ? a.M : a.Nc;
-  if (a.M < 1 || a.Nc < 1 || n > P1_SMALL) return hipErrorInvalidValue;
+  if (a.M < 1 || a.Nc < 1 || n > p1_small<T>()) return hipErrorInvalidValue;
   const dim3 g(a.nvec);
   if (n <= 16) hipLaunchKernelGGL((k_prec1d<T, 1>), g, dim3(64), 0, s, a);
   else if (n <= 32) hipLaunchKernelGGL((k_prec1d<T, 2>), g, dim3(256), 0, s, a);
   else if (n <= 48) hipLaunchKernelGGL((k_prec1d<T, 3>), g, dim3(576), 0, s, a);
-  else hipLaunchKernelGGL((k_prec1d<T, 4>), g, dim3(1024), 0, s, a);
+  else if constexpr (p1_small<T>() > 48) hipLaunchKernelGGL((k_prec1d<T, 4>), g, dim3(1024), 0, s, a);
   return hipGetLastError();
 }
 

@@ -414,7 +414,7 @@ static tp3b_status upload_ops(tp3b_op op, tp3b::DevOps<T>& d, const std::vector<
       TP3B_HIP(upload(&d.fLam[k], lam));
     }
   }
-  const bool prec1d = op->ndim == 1 && op->have_prec && std::max(op->n[0], op->n[1]) <= tp3b::P1_SMALL;
+  const bool prec1d = op->ndim == 1 && op->have_prec && std::max(op->n[0], op->n[1]) <= tp3b::p1_small<T>();
   if (op->plane2d || prec1d) {
     F.resize(tp3b::P2_FRAG);
     for (int k = 0; k < op->nmodes; ++k) {
@@ -600,7 +600,28 @@ ModeProd<T> prec_job(tp3b_op op, int st, int nv, const T* X, int64_t ldx, T* Y, 
   }
   return a;
 }
+template <typename T>
+bool prec_one(tp3b_op op, bool bf3) {
+  return op->ndim == 1 && dev_ops<T>(op).frSi[0] && !bf3 && op->tile_override < 0;
+}
+
+template <typename T>
+tp3b::Prec1D<T> prec1d_job(tp3b_op op, int nvec, const T* X, int64_t ldx, T* Y, int64_t ldy) {
+  DevOps<T>& d = dev_ops<T>(op);
+  tp3b::Prec1D<T> a{};
+  a.M = op->n[0]; a.Nc = op->n[1]; a.nvec = nvec;
+  a.X = X; a.Y = Y; a.ldx = ldx; a.ldy = ldy;
+  for (int k = 0; k < 2; ++k) {
+    a.FSi[k] = d.frSi[k];
+    a.FS[k] = d.frS[k];
+  }
+  a.lamL = d.lam[0]; a.lamR = d.lam[1];
+  a.sigma = op->sigma;
+  return a;
+}
 #define TP3B_JOBS(T)                                                                                  \
+  template bool prec_one<T>(tp3b_op, bool);                                                           \
+  template tp3b::Prec1D<T> prec1d_job<T>(tp3b_op, int, const T*, int64_t, T*, int64_t);               \
   template ModeProd<T> h_job<T>(tp3b_op, int, const T*, int64_t, T*, int64_t, const double*);          \
   template ModeProd<T> prec_job<T>(tp3b_op, int, int, const T*, int64_t, T*, int64_t, bool);
 TP3B_JOBS(double)
@@ -877,17 +898,8 @@ tp3b_status apply_prec_impl(tp3b_op op, int nvec, const T* X, int64_t ldx, T* Y,
   }
   // Z = Sx [ (Sx^{-1} B Sy^{-T}) / (lx_i + ly_j - sigma) ] Sy^T: one launch on small
   // grids (unless a product's tile is asked for), four mode products otherwise
-  if (d.frSi[0] && !bf3 && op->tile_override < 0) {
-    tp3b::Prec1D<T> a{};
-    a.M = op->n[0]; a.Nc = op->n[1]; a.nvec = nvec;
-    a.X = X; a.Y = Y; a.ldx = ldx; a.ldy = ldy;
-    for (int k = 0; k < 2; ++k) {
-      a.FSi[k] = d.frSi[k];
-      a.FS[k] = d.frS[k];
-    }
-    a.lamL = d.lam[0]; a.lamR = d.lam[1];
-    a.sigma = op->sigma;
-    TP3B_HIP(tp3b::launch_prec1d(a, s));
+  if (prec_one<T>(op, bf3)) {
+    TP3B_HIP(tp3b::launch_prec1d(prec1d_job<T>(op, nvec, X, ldx, Y, ldy), s));
     return TP3B_OK;
   }
   for (int v0 = 0; v0 < nvec; v0 += op->work_vecs) {
