@@ -352,9 +352,8 @@ __global__ __launch_bounds__(256) void k_dot_long(int64_t N, int p, int q, const
 // buffer of its own for the sum and 2048 workgroups of which 1536 were resident,
 // took longer: 40 columns against 8, N = 2^22, 355 us, and 90 us for the norms of
 // the eight in a pass of their own; both together now 330 us (4.9 TB/s, what a
-// copy reaches).  The last `self` columns of A may be those of B itself (their norms come with a dot that reads
-// B anyway).  Padding
-// columns load column 0 of their operand (their LDS entries feed only
+// copy reaches).  The last `self` columns of A may be those of B itself (their
+// norms come with a dot that reads B anyway).  Padding columns load column 0 of their operand (their LDS entries feed only
 // outputs outside p x q, which are not stored).  Requires aligned pairs of
 // rows: even leading dimensions and base pointers aligned to two elements.
 // rows of a step; wide tiles take half, or a CU would hold two workgroups
