@@ -55,7 +55,9 @@ __global__ __launch_bounds__(64 * WM * WN * SK) __attribute__((amdgpu_waves_per_
 }
 
 // Whether the kernel's 32-bit byte offsets reach every row that a chunk of the
-// tile spans.
+// tile spans: 16 FP64 or 32 FP32 rows of rs entries in the tiles without split K,
+// so rs up to 33,552,383.  The first x pass of 2D modes above 64 has rs = n_x n_y^2
+// and may reach further (8 x 8 x 2048 x 2048).
 template <typename G, typename T>
 static bool mp_reach(const ModeProd<T>& a) {
   const int64_t rows = std::max(a.LF ? (int)G::KT : 1, a.RF ? (int)G::TM : 1);
@@ -71,6 +73,27 @@ static void launch_mp(const ModeProd<T>& a, hipStream_t s) {
   }
   const unsigned grid = (unsigned)modeprod_items<G::TM, G::TN>(a);
   TP3B_MP_LAUNCH((k_modeprod<T, ROLE, MODE, BM, BN, WM, WN, SK>), grid, G::NT, s, a);
+}
+
+// Rows out of that reach: 64-bit offsets.  Such modes are short (8 rows of
+// 33,587,208 entries: FP64 2.2 ms, 1.9 TB/s), and the products of the padding to 64
+// rows, which cover the address arithmetic, take longer than the memory.
+template <typename T, int ROLE>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_modeprod_far(ModeProd<T> a) {
+  typedef MpTile<T, TP3B_MP_64> G;
+  __shared__ typename G::Smem sm;
+  mp_tile_w<T, TP3B_MP_64, MP_FAR, MP_PLAIN>(a, xcd_remap(blockIdx.x, modeprod_items<G::TM, G::TN>(a)), sm);
+}
+
+template <typename T, int ROLE>
+static hipError_t launch_far(const ModeProd<T>& a, hipStream_t s) {
+  typedef MpTile<T, TP3B_MP_64> G;
+  // the last mode's rows (right products) are at most 8192 long
+  if (a.RF || a.mode != MP_PLAIN) return hipErrorInvalidValue;
+  const int64_t items = modeprod_items<G::TM, G::TN>(a);
+  if (items >= (int64_t)1 << 31) return hipErrorInvalidValue;
+  TP3B_MP_LAUNCH((k_modeprod_far<T, ROLE>), (unsigned)items, G::NT, s, a);
+  return hipGetLastError();
 }
 
 template <typename T, int ROLE, int MODE>
@@ -92,7 +115,7 @@ hipError_t launch_modeprod(const ModeProd<T>& a, int tile, hipStream_t s) {
   if (tile < 0 || tile >= NUM_TILE_CFGS) return hipErrorInvalidValue;
   if (!a.LF && !a.RF) return hipErrorInvalidValue;
   tile = tile_of(tile, a.mode, sizeof(T) == 8);
-  if (!mp_reach<MpTile<T, TP3B_MP_128>>(a)) return hipErrorInvalidValue;  // N of 10^10 and more
+  if (!mp_reach<MpTile<T, TP3B_MP_128>>(a)) return a.acc ? launch_far<T, 2>(a, s) : launch_far<T, 1>(a, s);
   switch (a.mode) {
     case MP_FOLD_L: launch_role<T, 1, MP_FOLD_L>(a, tile, s); break;
     case MP_FOLD_R: launch_role<T, 1, MP_FOLD_R>(a, tile, s); break;

@@ -116,14 +116,18 @@ __device__ __forceinline__ P mp_load(__amdgpu_buffer_rsrc_t b, uint32_t off) {
 struct MpLeft { static constexpr bool left = true; };
 struct MpRight { static constexpr bool left = false; };
 
-// Output tile w of the product `a`.  WHOLE: the vector is read in whole pieces
-// (16-byte aligned rows, a multiple of a piece long).  MODE (MpMode): what the
-// product does to its operand or result besides:
+// How the vector is read: in whole pieces (16-byte aligned rows, a multiple of a
+// piece long), element by element, or element by element with 64-bit offsets (left
+// products whose chunks reach further than a buffer load's 32-bit offset).
+enum MpRead { MP_WHOLE, MP_ELEMENTS, MP_FAR };
+
+// Output tile w of the product `a`.  MODE (MpMode): what the product does to its
+// operand or result besides:
 //   fold    the operand is X[k] + X[k'] (item 0) or X[k] - X[k'] (item 1) with
 //           k' the mirror of k, formed while a chunk is put into LDS;
 //   unfold  two products over K, of the even and of the odd operand, whose sum
 //           and difference go to an output and its mirror.
-template <typename T, int BM, int BN, int WM, int WN, int SK, bool WHOLE, int MODE>
+template <typename T, int BM, int BN, int WM, int WN, int SK, int READ, int MODE>
 __device__ __forceinline__ void mp_tile_w(const ModeProd<T>& a, int64_t w,
                                           typename MpTile<T, BM, BN, WM, WN, SK>::Smem& sm) {
   typedef MpTile<T, BM, BN, WM, WN, SK> G;
@@ -132,8 +136,9 @@ __device__ __forceinline__ void mp_tile_w(const ModeProd<T>& a, int64_t w,
   typedef typename Mma<T>::acc_t acc_t;
   constexpr int KU = G::KU, BF = BM > BN ? BM : BN;
   constexpr bool FOLD = MODE == MP_FOLD_L || MODE == MP_FOLD_R, UNFOLD = MODE == MP_UNFOLD_L || MODE == MP_UNFOLD_R;
-  constexpr bool LEFT_ONLY = MODE == MP_FOLD_L || MODE == MP_UNFOLD_L;
+  constexpr bool LEFT_ONLY = MODE == MP_FOLD_L || MODE == MP_UNFOLD_L || READ == MP_FAR;
   constexpr bool RIGHT_ONLY = MODE == MP_FOLD_R || MODE == MP_UNFOLD_R;
+  static_assert(READ != MP_FAR || MODE == MP_PLAIN, "only plain products have rows this long");
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int lr = lane & 15, lk = lane >> 4;
   const int sk = wave / (WM * WN), wm = (wave / WN) % WM, wn = wave % WN;
@@ -196,7 +201,7 @@ __device__ __forceinline__ void mp_tile_w(const ModeProd<T>& a, int64_t w,
 
   piece raw[G::PM], mir[FOLD ? G::PM : 1];
   auto fetch = [&](__amdgpu_buffer_rsrc_t b, uint32_t off) -> piece {
-    if constexpr (WHOLE) {
+    if constexpr (READ == MP_WHOLE) {
       return mp_load<piece>(b, off);
     } else {
       T v[KU];
@@ -213,8 +218,20 @@ __device__ __forceinline__ void mp_tile_w(const ModeProd<T>& a, int64_t w,
     const int64_t at = (odd + (ph.left ? k0 * rs : i0 * rs + k0)) * ES;
     const __amdgpu_buffer_rsrc_t b = mp_buffer((const char*)X + at, odd * ES + extent - at);
     constexpr int P = ph.left ? G::PL : G::PR;
+    if constexpr (READ == MP_FAR && ph.left) {
+      // (as the buffer reads: rows past the vector are zero)
 #pragma unroll
-    for (int s = 0; s < P; ++s) raw[s] = fetch(b, ph.left ? vl[s % G::PL] : vr[s % G::PR]);
+      for (int s = 0; s < P; ++s) {
+        const int64_t e = (k0 + rl + s * DL) * rs + j0 + cl;
+        T v[KU];
+#pragma unroll
+        for (int u = 0; u < KU; ++u) v[u] = (e + u) * (int64_t)ES < extent ? X[e + u] : T(0);
+        raw[s] = __builtin_bit_cast(piece, v);
+      }
+    } else {
+#pragma unroll
+      for (int s = 0; s < P; ++s) raw[s] = fetch(b, ph.left ? vl[s % G::PL] : vr[s % G::PR]);
+    }
     if constexpr (FOLD) {
       // the mirrors: rows full-1-k, or columns full-1-k in reverse order.  Places
       // before the vector's start (k past the half) wrap to offsets past its end.
@@ -226,7 +243,7 @@ __device__ __forceinline__ void mp_tile_w(const ModeProd<T>& a, int64_t w,
         } else {
           const uint32_t row = (uint32_t)(i0 + rr + s * DR) * rsb;
           const int first = full - KU - k0 - cr;  // mirror of the piece's last k
-          if constexpr (WHOLE) {
+          if constexpr (READ == MP_WHOLE) {
             mir[s] = fetch(m, row + (uint32_t)first * ES);
           } else {
             // a piece of a short row may start before it: those are k past the half
@@ -346,7 +363,7 @@ __device__ __forceinline__ void mp_tile_w(const ModeProd<T>& a, int64_t w,
     __syncthreads();
   };
   acc_t even[UNFOLD ? BM : 1][UNFOLD ? BN : 1];
-  if constexpr (MODE == MP_PLAIN) {
+  if constexpr (MODE == MP_PLAIN && !LEFT_ONLY) {
     if (nL) start(MpLeft());
     else start(MpRight());
     int c = 0;
@@ -546,9 +563,9 @@ __device__ __forceinline__ void mp_tile(const ModeProd<T>& a, int64_t w,
                      (MODE != MP_PLAIN || (a.Nc % KU == 0 && a.bstride % KU == 0)) &&
                      (MODE != MP_FOLD_R || a.full % KU == 0);
   if (MODE == MP_UNFOLD_L || MODE == MP_UNFOLD_R || whole)
-    mp_tile_w<T, BM, BN, WM, WN, SK, true, MODE>(a, w, sm);
+    mp_tile_w<T, BM, BN, WM, WN, SK, MP_WHOLE, MODE>(a, w, sm);
   else
-    mp_tile_w<T, BM, BN, WM, WN, SK, false, MODE>(a, w, sm);
+    mp_tile_w<T, BM, BN, WM, WN, SK, MP_ELEMENTS, MODE>(a, w, sm);
 }
 
 // The tile shapes of TileCfg: (BM, BN, WM, WN, SK).
