@@ -15,6 +15,7 @@
 // device addresses; with opts.graph it is captured once as a HIP graph and
 // replayed in every outer iteration after the tables have been rewritten.
 #include <algorithm>
+#include <array>
 #include <utility>
 #include <chrono>
 #include <cmath>
@@ -106,27 +107,34 @@ hipError_t mp_launch(const MpTabs<float>& m, hipStream_t s) {
   return hipSuccess;
 }
 
-// The tables of one grouped preconditioner apply: four steps, each as plain and
-// as folded products, and the applies of one launch (an instance has its job in
-// one of the three).
+// The tables of one grouped preconditioner apply: four steps of plain products, the
+// same folded for each group of vectors, and the applies of one launch (an instance
+// has its jobs in one of the three).
 template <typename T>
 struct PrecTabs {
-  MpTabs<T> mp[2][4];
-  bool use[2] = {false, false};
+  typedef std::array<MpTabs<T>, 4> Steps;
+  Steps plain;
+  std::vector<Steps> fold;
   Tab<Prec1D<T>> one;
-  bool use_one = false;
+  bool use_plain = false, use_one = false;
 };
 
+// For applies of up to nvec vectors.
 template <typename T>
-bool prec_alloc(TableArena& ar, const tp3b_op* ops, int count, const TileSet& ts, int cap, bool bf3, PrecTabs<T>& p) {
+bool prec_alloc(TableArena& ar, const tp3b_op* ops, int count, const TileSet& ts, int cap, int nvec, bool bf3,
+                PrecTabs<T>& p) {
+  int groups = 0;
   for (int i = 0; i < count; ++i)
     if (prec_one<T>(ops[i], bf3)) p.use_one = true;
-    else p.use[prec_folded(ops[i], bf3)] = true;
+    else if (prec_folded(ops[i], bf3)) groups = std::max(groups, ops[i]->fold_groups(nvec));
+    else p.use_plain = true;
+  p.fold.assign(groups, {});
   bool ok = !p.use_one || ar.alloc(p.one, cap);
-  for (int f = 0; f < 2; ++f)
-    for (int st = 0; st < 4 && p.use[f]; ++st) {
-      ok = ok && mp_alloc(ar, ts, cap, bf3, p.mp[f][st]);
-      if (f) p.mp[f][st].mode = MP_FOLD_L + st;
+  for (int st = 0; st < 4 && p.use_plain; ++st) ok = ok && mp_alloc(ar, ts, cap, bf3, p.plain[st]);
+  for (auto& g : p.fold)
+    for (int st = 0; st < 4; ++st) {
+      ok = ok && mp_alloc(ar, ts, cap, bf3, g[st]);
+      g[st].mode = MP_FOLD_L + st;
     }
   return ok;
 }
@@ -138,17 +146,25 @@ bool prec_add(PrecTabs<T>& p, tp3b_op op, bool bf3, int nv, const T* X, int64_t 
     return true;
   }
   const bool fold = prec_folded(op, bf3);
-  for (int st = 0; st < 4; ++st)
-    if (!mp_add(p.mp[fold][st], prec_job<T>(op, st, nv, X, ldx, Y, ldy, fold), tile)) return false;
+  const int step = fold ? op->fold_step(nv) : nv;
+  for (int u = 0; u < nv; u += step) {
+    auto& steps = fold ? p.fold[u / step] : p.plain;
+    for (int st = 0; st < 4; ++st)
+      if (!mp_add(steps[st], prec_job<T>(op, st, std::min(step, nv - u), X + u * ldx, ldx, Y + u * ldy, ldy, fold), tile))
+        return false;
+  }
   return true;
 }
 
 template <typename T>
 hipError_t prec_launch(const PrecTabs<T>& p, hipStream_t s) {
   hipError_t e = p.use_one ? launch_prec1d_grouped<T>(p.one.d, s) : hipSuccess;
-  for (int st = 0; st < 4; ++st)
-    for (int f = 0; f < 2 && e == hipSuccess; ++f)
-      if (p.use[f]) e = mp_launch(p.mp[f][st], s);
+  for (int st = 0; st < 4 && e == hipSuccess; ++st) {
+    if (p.use_plain) e = mp_launch(p.plain[st], s);
+    if (!p.fold.empty() && e == hipSuccess) e = mp_launch(p.fold[0][st], s);
+  }
+  for (size_t g = 1; g < p.fold.size(); ++g)
+    for (int st = 0; st < 4 && e == hipSuccess; ++st) e = mp_launch(p.fold[g][st], s);
   return e;
 }
 
@@ -193,7 +209,7 @@ tp3b_status apply_batched(const tp3b_op* ops, int count, int nvec, const void* c
   for (int i = 0; i < count; ++i) ts.add(op_tile(ops[i], f64, bf3, prec ? 1 : 0, nvec));
   MpTabs<T> h;
   PrecTabs<T> p;
-  if (!(prec ? prec_alloc(*ar, ops, count, ts, count, bf3, p) : mp_alloc(*ar, ts, count, bf3, h)))
+  if (!(prec ? prec_alloc(*ar, ops, count, ts, count, nvec, bf3, p) : mp_alloc(*ar, ts, count, bf3, h)))
     return arena_full();
   for (int i = 0; i < count; ++i) {
     const T* x = (const T*)X[i];
@@ -496,7 +512,8 @@ tp3b_status BatchedJdqr<TW>::prec64(const std::vector<int>& list,
   if (list.empty()) return TP3B_OK;
   TP3B_TRY(arena_room());
   PrecTabs<double> t;
-  if (!prec_alloc(ar_, ops_, count_, tsP64_, (int)list.size(), false, t)) return arena_full();
+  const int most = std::max(1, *std::max_element(nv.begin(), nv.end()));
+  if (!prec_alloc(ar_, ops_, count_, tsP64_, (int)list.size(), most, false, t)) return arena_full();
   for (size_t e = 0; e < list.size(); ++e) {
     if (nv[e] <= 0) continue;
     const Inst& I = in_[list[e]];
@@ -790,7 +807,7 @@ tp3b_status BatchedJdqr<TW>::build_gmres_tables() {
   g.bu2.assign(steps_, Tab<BupdJob<TW>>());
   g.normk.assign(steps_, Tab<NormJob<TW>>());
   bool ok = gar_.alloc(g.rhs_conv, cap);
-  ok = ok && prec_alloc(gar_, ops_, count_, tsPW_, cap, bf3_, g.prec);
+  ok = ok && prec_alloc(gar_, ops_, count_, tsPW_, cap, b_, bf3_, g.prec);
   ok = ok && gar_.alloc(g.proj_dot, cap) && gar_.alloc(g.proj_gemm, cap) && gar_.alloc(g.nrm, cap) &&
        gar_.alloc(g.norm0, cap);
   for (int kk = 0; kk < steps_; ++kk) {

@@ -38,7 +38,7 @@ struct DevOps {
   T* lam[4] = {nullptr, nullptr, nullptr, nullptr};
   T* lamItem = nullptr;  // 2D: lam_x1[i1] + lam_x2[i2] per (x1, x2) plane
   T* lamItemY = nullptr;  // 2D: lam_y1[j1] + lam_y2[j2] per flattened y index
-  T* work = nullptr;  // preconditioner intermediate, work_vecs vectors
+  T* work = nullptr;  // preconditioner intermediates, N work_vecs entries
   // 2D operators with every mode size <= P2_MAXN: MFMA fragments (plane2d.hip)
   // of K_k, S_k and S_k^{-1} per mode, and the separable factors of a Gaussian
   // potential (4 x 64 x 64, NULL for other potentials).  frS and frSi also for 1D
@@ -114,11 +114,16 @@ struct tp3b_op_s {
   tp3b::DevOps<double> d64;
   tp3b::DevOps<float> d32;
   int work_vecs = 0;
-  // 1D, both mode matrices symmetric under the reflection of their grid: the
-  // preconditioner runs as folded products (MpMode), and the work buffer holds
-  // two blocks of work_vecs vectors of fold_size entries
+  // 1D, both mode matrices symmetric under the reflection of their grid, N large
+  // enough: the preconditioner runs as folded products (MpMode) over groups of up to
+  // fold_vecs vectors, as many as the work buffer holds in two blocks of fold_size
+  // entries per vector
   bool fold = false;
+  int fold_vecs = 0;
   int64_t fold_size() const { return 4 * (int64_t)tp3b::fold_half(n[0]) * tp3b::fold_row(n[1]); }
+  // vectors per group when nv vectors go through folded (groups of nearly equal size)
+  int fold_groups(int nv) const { return (nv + fold_vecs - 1) / fold_vecs; }
+  int fold_step(int nv) const { return (nv + fold_groups(nv) - 1) / fold_groups(nv); }
   bool plane2d = false;         // 2D with every mode size <= P2_MAXN: two-pass applies
   bool x_same_K = false;        // 2D: the two x modes have the same operator K (and
   bool x_same_S = false;        // the same eigen-factors): one LDS copy in the x passes
@@ -169,7 +174,7 @@ tp3b_status apply_prec_impl(tp3b_op op, int nvec, const T* X, int64_t ldx, T* Y,
 // Hamiltonian apply, and stage st (0..3) of the preconditioner
 // Z = Sx [(Sx^{-1} B Sy^{-T}) / (lx_i + ly_j - sigma)] Sy^T, whose intermediates
 // live in the operator's work buffer (and, in the plain form, in Y); nv <=
-// work_vecs.
+// work_vecs, folded nv <= fold_vecs.
 template <typename T>
 ModeProd<T> h_job(tp3b_op op, int nvec, const T* X, int64_t ldx, T* Y, int64_t ldy, const double* shifts);
 template <typename T>

@@ -383,9 +383,7 @@ static tp3b_status upload_ops(tp3b_op op, tp3b::DevOps<T>& d, const std::vector<
       TP3B_HIP(upload(&d.lamItem, pf.lamItem));
       TP3B_HIP(upload(&d.lamItemY, pf.lamItemY));
     }
-    // 1D with folded products: two blocks
-    const int64_t per = op->fold ? std::max(op->N, 2 * op->fold_size()) : op->N;
-    TP3B_HIP(hipMalloc((void**)&d.work, sizeof(T) * per * op->work_vecs));
+    TP3B_HIP(hipMalloc((void**)&d.work, sizeof(T) * op->N * op->work_vecs));
   }
   if (op->fold && op->have_prec) {
     for (int k = 0; k < 2; ++k) {
@@ -530,11 +528,7 @@ ModeProd<T> h_job(tp3b_op op, int nvec, const T* X, int64_t ldx, T* Y, int64_t l
   return a;
 }
 
-// Small grids keep the plain products: their four launches are bound by latency,
-// which the folds add to.  Us per apply, plain / folded: 128 x 128 x 8 19.2 / 19.8
-// (FP32 17.4 / 19.4), 256 x 128 x 4 22.1 / 23.2, 256 x 256 x 8 36.9 / 30.7 (FP32
-// 26.2 / 22.0), 512 x 512 x 8 156 / 108, 1024 x 1024 x 16 1953 / 1097.
-bool prec_folded(tp3b_op op, bool bf3) { return op->fold && !bf3 && op->N > 32768; }
+bool prec_folded(tp3b_op op, bool bf3) { return op->fold && !bf3; }
 
 template <typename T>
 ModeProd<T> prec_job(tp3b_op op, int st, int nv, const T* X, int64_t ldx, T* Y, int64_t ldy, bool fold) {
@@ -554,7 +548,7 @@ ModeProd<T> prec_job(tp3b_op op, int st, int nv, const T* X, int64_t ldx, T* Y, 
     const int nx = op->n[0], ny = op->n[1], hx = fold_half(nx), hy = fold_half(ny), ry = fold_row(ny);
     const int64_t nc4 = (ny + 3) / 4 * 4, sz = op->fold_size();
     T* w0 = d.work;
-    T* w1 = d.work + sz * op->work_vecs;
+    T* w1 = d.work + sz * op->fold_vecs;
     a.ldx = a.ldy = sz;
     const int k = st % 2, h = k ? hy : hx;
     (k ? a.RF : a.LF) = st < 2 ? d.fSi[k] : d.fS[k];
@@ -906,9 +900,11 @@ tp3b_status apply_prec_impl(tp3b_op op, int nvec, const T* X, int64_t ldx, T* Y,
     const T* Xv = X + (int64_t)v0 * ldx;
     T* Yv = Y + (int64_t)v0 * ldy;
     const bool fold = prec_folded(op, bf3);
-    const int tile = op_tile(op, f64, bf3, 1, nv);
-    for (int st = 0; st < 4; ++st)
-      TP3B_HIP(modeprod(op, prec_job<T>(op, st, nv, Xv, ldx, Yv, ldy, fold), tile, s, bf3));
+    const int tile = op_tile(op, f64, bf3, 1, nv), step = fold ? op->fold_step(nv) : nv;
+    for (int u = 0; u < nv; u += step)
+      for (int st = 0; st < 4; ++st)
+        TP3B_HIP(modeprod(op, prec_job<T>(op, st, std::min(step, nv - u), Xv + u * ldx, ldx, Yv + u * ldy, ldy, fold),
+                          tile, s, bf3));
   }
   return TP3B_OK;
 }
@@ -1380,7 +1376,14 @@ tp3b_status tp3b_create(const tp3b_problem_desc* desc, void* stream, tp3b_op* ou
       op->y_same_K = Kh[2] == Kh[3];
       op->y_same_S = op->have_prec && pf.S[2] == pf.S[3] && pf.Si[2] == pf.Si[3];
     }
-    op->fold = op->ndim == 1 && reflection_symmetric(desc, 0, Kh[0]) && reflection_symmetric(desc, 1, Kh[1]);
+    // Small grids keep the plain products: their four launches are bound by latency,
+    // which the folds add to.  Us per apply, plain / folded: 128 x 128 x 8 19.2 / 19.8
+    // (FP32 17.4 / 19.4), 256 x 128 x 4 22.1 / 23.2, 256 x 256 x 8 36.9 / 30.7 (FP32
+    // 26.2 / 22.0), 512 x 512 x 8 156 / 108, 1024 x 1024 x 16 1953 / 1097.
+    if (op->ndim == 1 && N > 32768 && reflection_symmetric(desc, 0, Kh[0]) && reflection_symmetric(desc, 1, Kh[1])) {
+      op->fold_vecs = (int)(op->work_vecs * N / (2 * op->fold_size()));
+      op->fold = op->fold_vecs > 0;
+    }
     tp3b_status st = upload_ops<double>(op, op->d64, Kh, pf);
     if (st == TP3B_OK) st = upload_ops<float>(op, op->d32, Kh, pf);
     if (st == TP3B_OK) st = bf3_split_ops(op);
