@@ -46,66 +46,78 @@ using Tab = TableArena::Tab<Job>;
 
 tp3b_status arena_full() { return fail(TP3B_ENOMEM, "batched: job-table arena exhausted"); }
 
-// Tile shapes in use by one kind of mode-product step over a batch.
+// Instances per tile shape in one kind of mode-product step over a batch.
 struct TileSet {
-  int n = 0;
-  int id[NUM_TILE_CFGS] = {};
-  void add(int t) {
-    for (int i = 0; i < n; ++i)
-      if (id[i] == t) return;
-    id[n++] = t;
-  }
+  int cap[NUM_TILE_CFGS] = {};
+  void add(int t) { ++cap[t]; }
 };
 
-// The tables of one grouped mode-product step, one per tile shape in use.
+// The tables of one grouped mode-product step, one per tile shape in use, each as
+// large as the instances that use it.
 template <typename T>
 struct MpTabs {
-  int n = 0;
-  int tile[NUM_TILE_CFGS] = {};
   Tab<ModeProd<T>> t[NUM_TILE_CFGS];
   bool bf3 = false;
   int mode = MP_PLAIN;
 };
 
+// For at most `cap` instances of the set.
 template <typename T>
 bool mp_alloc(TableArena& ar, const TileSet& ts, int cap, bool bf3, MpTabs<T>& m) {
-  m.n = ts.n;
   m.bf3 = bf3;
-  for (int i = 0; i < ts.n; ++i) {
-    m.tile[i] = ts.id[i];
-    if (!ar.alloc(m.t[i], cap)) return false;
-  }
+  for (int i = 0; i < NUM_TILE_CFGS; ++i)
+    if (ts.cap[i] > 0 && !ar.alloc(m.t[i], std::min(ts.cap[i], cap))) return false;
   return true;
 }
 
-// Adds a job to the table of its tile shape; false if no table has that shape.
+// Adds a job to the table of its tile shape; false if no table has room for it.
 template <typename T>
 bool mp_add(MpTabs<T>& m, const ModeProd<T>& a, int tile) {
-  for (int i = 0; i < m.n; ++i)
-    if (m.tile[i] == tile) {
-      TableArena::add(m.t[i], a, modeprod_items_for(a.M, a.Nc, a.nbatch, m.bf3 ? tile : tile_of(tile, a.mode, sizeof(T) == 8), m.bf3));
-      return true;
-    }
-  return false;
+  Tab<ModeProd<T>>& t = m.t[tile];
+  if (!t.h || t.njobs() >= t.cap) return false;
+  TableArena::add(t, a, modeprod_items_for(a.M, a.Nc, a.nbatch, m.bf3 ? tile : tile_of(tile, a.mode, sizeof(T) == 8), m.bf3));
+  return true;
 }
 
 tp3b_status tile_missing() { return fail(TP3B_EDEVICE, "batched: tile shape without a job table"); }
 
 hipError_t mp_launch(const MpTabs<double>& m, hipStream_t s) {
-  for (int i = 0; i < m.n; ++i) {
-    hipError_t e = launch_modeprod_grouped<double>(m.t[i].d, m.tile[i], m.mode, s);
+  for (int i = 0; i < NUM_TILE_CFGS; ++i) {
+    if (!m.t[i].h) continue;
+    hipError_t e = launch_modeprod_grouped<double>(m.t[i].d, i, m.mode, s);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
 }
 hipError_t mp_launch(const MpTabs<float>& m, hipStream_t s) {
-  for (int i = 0; i < m.n; ++i) {
-    hipError_t e = m.bf3 ? launch_modeprod_bf3_grouped(m.t[i].d, m.tile[i], s)
-                         : launch_modeprod_grouped<float>(m.t[i].d, m.tile[i], m.mode, s);
+  for (int i = 0; i < NUM_TILE_CFGS; ++i) {
+    if (!m.t[i].h) continue;
+    hipError_t e = m.bf3 ? launch_modeprod_bf3_grouped(m.t[i].d, i, s)
+                         : launch_modeprod_grouped<float>(m.t[i].d, i, m.mode, s);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
 }
+
+// The instances of a batch by the form of their preconditioner applies, for up to
+// nvec vectors.
+struct PrecSet {
+  TileSet plain;
+  std::vector<TileSet> fold;  // per group of vectors
+  int one = 0;
+  template <typename T>
+  void add(tp3b_op op, bool bf3, int tile, int nvec) {
+    if (prec_one<T>(op, bf3)) {
+      ++one;
+    } else if (prec_folded(op, bf3)) {
+      const size_t groups = op->fold_groups(nvec);
+      if (fold.size() < groups) fold.resize(groups);
+      for (size_t g = 0; g < groups; ++g) fold[g].add(tile);
+    } else {
+      plain.add(tile);
+    }
+  }
+};
 
 // The tables of one grouped preconditioner apply: four steps of plain products, the
 // same folded for each group of vectors, and the applies of one launch (an instance
@@ -116,25 +128,18 @@ struct PrecTabs {
   Steps plain;
   std::vector<Steps> fold;
   Tab<Prec1D<T>> one;
-  bool use_plain = false, use_one = false;
 };
 
-// For applies of up to nvec vectors.
+// For at most `cap` instances of the set.
 template <typename T>
-bool prec_alloc(TableArena& ar, const tp3b_op* ops, int count, const TileSet& ts, int cap, int nvec, bool bf3,
-                PrecTabs<T>& p) {
-  int groups = 0;
-  for (int i = 0; i < count; ++i)
-    if (prec_one<T>(ops[i], bf3)) p.use_one = true;
-    else if (prec_folded(ops[i], bf3)) groups = std::max(groups, ops[i]->fold_groups(nvec));
-    else p.use_plain = true;
-  p.fold.assign(groups, {});
-  bool ok = !p.use_one || ar.alloc(p.one, cap);
-  for (int st = 0; st < 4 && p.use_plain; ++st) ok = ok && mp_alloc(ar, ts, cap, bf3, p.plain[st]);
-  for (auto& g : p.fold)
+bool prec_alloc(TableArena& ar, const PrecSet& ps, int cap, bool bf3, PrecTabs<T>& p) {
+  p.fold.assign(ps.fold.size(), {});
+  bool ok = ps.one == 0 || ar.alloc(p.one, std::min(ps.one, cap));
+  for (int st = 0; st < 4; ++st) ok = ok && mp_alloc(ar, ps.plain, cap, bf3, p.plain[st]);
+  for (size_t g = 0; g < ps.fold.size(); ++g)
     for (int st = 0; st < 4; ++st) {
-      ok = ok && mp_alloc(ar, ts, cap, bf3, g[st]);
-      g[st].mode = MP_FOLD_L + st;
+      ok = ok && mp_alloc(ar, ps.fold[g], cap, bf3, p.fold[g][st]);
+      p.fold[g][st].mode = MP_FOLD_L + st;
     }
   return ok;
 }
@@ -142,12 +147,14 @@ bool prec_alloc(TableArena& ar, const tp3b_op* ops, int count, const TileSet& ts
 template <typename T>
 bool prec_add(PrecTabs<T>& p, tp3b_op op, bool bf3, int nv, const T* X, int64_t ldx, T* Y, int64_t ldy, int tile) {
   if (prec_one<T>(op, bf3)) {
+    if (!p.one.h || p.one.njobs() >= p.one.cap) return false;
     TableArena::add(p.one, prec1d_job<T>(op, nv, X, ldx, Y, ldy), nv);
     return true;
   }
   const bool fold = prec_folded(op, bf3);
   const int step = fold ? op->fold_step(nv) : nv;
   for (int u = 0; u < nv; u += step) {
+    if (fold && (size_t)(u / step) >= p.fold.size()) return false;
     auto& steps = fold ? p.fold[u / step] : p.plain;
     for (int st = 0; st < 4; ++st)
       if (!mp_add(steps[st], prec_job<T>(op, st, std::min(step, nv - u), X + u * ldx, ldx, Y + u * ldy, ldy, fold), tile))
@@ -158,9 +165,9 @@ bool prec_add(PrecTabs<T>& p, tp3b_op op, bool bf3, int nv, const T* X, int64_t 
 
 template <typename T>
 hipError_t prec_launch(const PrecTabs<T>& p, hipStream_t s) {
-  hipError_t e = p.use_one ? launch_prec1d_grouped<T>(p.one.d, s) : hipSuccess;
+  hipError_t e = p.one.h ? launch_prec1d_grouped<T>(p.one.d, s) : hipSuccess;
   for (int st = 0; st < 4 && e == hipSuccess; ++st) {
-    if (p.use_plain) e = mp_launch(p.plain[st], s);
+    e = mp_launch(p.plain[st], s);
     if (!p.fold.empty() && e == hipSuccess) e = mp_launch(p.fold[0][st], s);
   }
   for (size_t g = 1; g < p.fold.size(); ++g)
@@ -187,7 +194,9 @@ TableArena* apply_arena() {
   static thread_local std::unique_ptr<TableArena> ar;
   if (!ar) {
     ar.reset(new TableArena());
-    if (ar->init((size_t)16 << 20) != hipSuccess) {
+    // per instance 224 bytes for H and four times that for the preconditioner, twice
+    // that where folded applies take two groups of vectors
+    if (ar->init((size_t)24 << 20) != hipSuccess) {
       ar.reset();
       return nullptr;
     }
@@ -206,10 +215,15 @@ tp3b_status apply_batched(const tp3b_op* ops, int count, int nvec, const void* c
   ar->reset();
   const bool f64 = sizeof(T) == 8;
   TileSet ts;
-  for (int i = 0; i < count; ++i) ts.add(op_tile(ops[i], f64, bf3, prec ? 1 : 0, nvec));
+  PrecSet ps;
+  for (int i = 0; i < count; ++i) {
+    const int tile = op_tile(ops[i], f64, bf3, prec ? 1 : 0, nvec);
+    if (prec) ps.add<T>(ops[i], bf3, tile, nvec);
+    else ts.add(tile);
+  }
   MpTabs<T> h;
   PrecTabs<T> p;
-  if (!(prec ? prec_alloc(*ar, ops, count, ts, count, nvec, bf3, p) : mp_alloc(*ar, ts, count, bf3, h)))
+  if (!(prec ? prec_alloc(*ar, ps, count, bf3, p) : mp_alloc(*ar, ts, count, bf3, h)))
     return arena_full();
   for (int i = 0; i < count; ++i) {
     const T* x = (const T*)X[i];
@@ -324,7 +338,7 @@ class BatchedJdqr {
   // Tables are appended to the phase arena without waiting; only when it runs
   // low does the stream have to drain first.
   tp3b_status arena_room() {
-    if (ar_.free_bytes() < ((size_t)4 << 20)) return sync();
+    if (ar_.free_bytes() < std::max((size_t)6 << 20, (size_t)1024 * count_)) return sync();
     return TP3B_OK;
   }
   // ---- the GMRES phase
@@ -346,7 +360,8 @@ class BatchedJdqr {
   void* smallbuf_ = nullptr;
   TableArena ar_;     // tables rebuilt freely within a phase
   TableArena gar_;    // GMRES tables (same layout every outer iteration)
-  TileSet tsH64_, tsHW_, tsP64_, tsPW_;
+  TileSet tsH64_, tsHW_;
+  PrecSet tsP64_, tsPW_;
   Small S_, Tb_, Mf_, Top_, Left_, Cq1_, Cq2_, Nrm_, Hh_, Hinv_, Shift_, C2_, H1_, H2_, Hs_,
       Beta_, Y_, G_, R1_, R2_, n0_, Co1_, Co2_, FlagsD_;
   hipGraphExec_t gexec_ = nullptr;
@@ -468,7 +483,7 @@ tp3b_status BatchedJdqr<TW>::setup() {
   }
   for (int i = 0; i < count_; ++i) in_[i].flags = (int*)FlagsD_.at(i);
   // ---- job-table arenas
-  TP3B_HIP(ar_.init((size_t)40 << 20));
+  TP3B_HIP(ar_.init((size_t)48 << 20));
   TP3B_HIP(gar_.init((size_t)80 << 20));
   // ---- tile shapes
   for (int i = 0; i < count_; ++i) {
@@ -479,8 +494,9 @@ tp3b_status BatchedJdqr<TW>::setup() {
     I.tPW = op_tile(ops_[i], !low_, bf3_, 1, b_);
     tsH64_.add(I.tH64);
     tsHW_.add(I.tHW);
-    tsP64_.add(I.tP64);
-    tsPW_.add(I.tPW);
+    // (the FP64 applies take the block or the pairs that lock)
+    tsP64_.add<double>(I.op, false, I.tP64, std::max(b_, nev_));
+    tsPW_.add<TW>(I.op, bf3_, I.tPW, b_);
   }
   return TP3B_OK;
 }
@@ -512,8 +528,7 @@ tp3b_status BatchedJdqr<TW>::prec64(const std::vector<int>& list,
   if (list.empty()) return TP3B_OK;
   TP3B_TRY(arena_room());
   PrecTabs<double> t;
-  const int most = std::max(1, *std::max_element(nv.begin(), nv.end()));
-  if (!prec_alloc(ar_, ops_, count_, tsP64_, (int)list.size(), most, false, t)) return arena_full();
+  if (!prec_alloc(ar_, tsP64_, (int)list.size(), false, t)) return arena_full();
   for (size_t e = 0; e < list.size(); ++e) {
     if (nv[e] <= 0) continue;
     const Inst& I = in_[list[e]];
@@ -807,7 +822,7 @@ tp3b_status BatchedJdqr<TW>::build_gmres_tables() {
   g.bu2.assign(steps_, Tab<BupdJob<TW>>());
   g.normk.assign(steps_, Tab<NormJob<TW>>());
   bool ok = gar_.alloc(g.rhs_conv, cap);
-  ok = ok && prec_alloc(gar_, ops_, count_, tsPW_, cap, b_, bf3_, g.prec);
+  ok = ok && prec_alloc(gar_, tsPW_, cap, bf3_, g.prec);
   ok = ok && gar_.alloc(g.proj_dot, cap) && gar_.alloc(g.proj_gemm, cap) && gar_.alloc(g.nrm, cap) &&
        gar_.alloc(g.norm0, cap);
   for (int kk = 0; kk < steps_; ++kk) {
