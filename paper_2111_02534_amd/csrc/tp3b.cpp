@@ -292,7 +292,10 @@ struct PrecFactors {
 
 // Eigen-factors of a reflection-symmetric mode operator from those of its even
 // and odd halves (a quarter of the work of the whole matrix): the even
-// eigenvectors are (u, u mirrored), the odd ones (u, -u mirrored).
+// eigenvectors are (u, u mirrored), the odd ones (u, -u mirrored), each of length 1
+// as eigen_decompose_real gives them: with the halves' columns of length 1 instead,
+// other bits of the factors are cut when BF16x3 splits them (n = 1024, 16 vectors:
+// error of the preconditioner 9.6e-6 instead of 8.7e-6).
 static bool parity_decompose(int n, const std::vector<double>& K, PrecFactors& pf, int k) {
   const int h[2] = {(n + 1) / 2, n / 2};
   pf.S[k].assign((size_t)n * n, 0.0);
@@ -310,12 +313,17 @@ static bool parity_decompose(int n, const std::vector<double>& K, PrecFactors& p
     S.resize((size_t)m * m);
     Si.resize((size_t)m * m);
     if (!eigen_decompose_real(m, A.data(), S.data(), Si.data(), pf.lam[k].data() + c0)) return false;
+    std::vector<double> len(m, 0.0);
+    for (int i = 0; i < m; ++i)
+      for (int c = 0; c < m; ++c) len[c] += (n - 1 - i != i ? 2.0 : 1.0) * S[(size_t)i * m + c] * S[(size_t)i * m + c];
+    for (double& l : len) l = std::sqrt(l);
     for (int i = 0; i < m; ++i) {
       const int i2 = n - 1 - i;
       for (int c = 0; c < m; ++c) {
-        pf.S[k][(size_t)i * n + c0 + c] = S[(size_t)i * m + c];
-        if (i2 != i) pf.S[k][(size_t)i2 * n + c0 + c] = sg * S[(size_t)i * m + c];
-        const double v = Si[(size_t)c * m + i] * (i2 != i ? 0.5 : 1.0);
+        const double u = S[(size_t)i * m + c] / len[c];
+        pf.S[k][(size_t)i * n + c0 + c] = u;
+        if (i2 != i) pf.S[k][(size_t)i2 * n + c0 + c] = sg * u;
+        const double v = Si[(size_t)c * m + i] * len[c] * (i2 != i ? 0.5 : 1.0);
         pf.Si[k][(size_t)(c0 + c) * n + i] = v;
         if (i2 != i) pf.Si[k][(size_t)(c0 + c) * n + i2] = sg * v;
       }
