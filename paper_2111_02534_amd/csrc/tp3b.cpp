@@ -280,29 +280,29 @@ static std::vector<double> transpose(const std::vector<double>& A, int n) {
   return B;
 }
 
+// Up to this many points the preconditioner keeps the plain products: their four
+// launches are bound by latency, which the folds add to.  Us per apply, plain /
+// folded: 128 x 128 x 8 19.2 / 19.8 (FP32 17.4 / 19.4), 256 x 128 x 4 22.1 / 23.2,
+// 256 x 256 x 8 36.9 / 30.7 (FP32 26.2 / 22.0), 512 x 512 x 8 156 / 108,
+// 1024 x 1024 x 16 1953 / 1097.
+constexpr int64_t kFoldMin = 32768;
+
 // Host eigen-factors of the kinetic mode operators K_k = S_k diag(lam_k) S_k^{-1}.
 struct PrecFactors {
   std::vector<double> S[4], Si[4], lam[4];
   // reflection-symmetric modes: the factors of the even [0] and odd [1] half,
-  // ceil(n/2) and floor(n/2) wide (lam holds the even eigenvalues first)
-  std::vector<double> SF[4][2], SiF[4][2];
+  // ceil(n/2) and floor(n/2) wide, and the eigenvalues, the even ones first
+  std::vector<double> SF[4][2], SiF[4][2], lamF[4];
   std::vector<double> lamItem;   // 2D: lam_0[i1] + lam_1[i2]
   std::vector<double> lamItemY;  // 2D: lam_2[j1] + lam_3[j2]
 };
 
-// Eigen-factors of a reflection-symmetric mode operator from those of its even
-// and odd halves (a quarter of the work of the whole matrix): the even
-// eigenvectors are (u, u mirrored), the odd ones (u, -u mirrored), each of length 1
-// as eigen_decompose_real gives them: with the halves' columns of length 1 instead,
-// other bits of the factors are cut when BF16x3 splits them (n = 1024, 16 vectors:
-// error of the preconditioner 9.6e-6 instead of 8.7e-6).
-static bool parity_decompose(int n, const std::vector<double>& K, PrecFactors& pf, int k) {
+// Eigen-factors of the even and odd halves of a reflection-symmetric mode operator.
+static bool parity_halves(int n, const std::vector<double>& K, PrecFactors& pf, int k) {
   const int h[2] = {(n + 1) / 2, n / 2};
-  pf.S[k].assign((size_t)n * n, 0.0);
-  pf.Si[k].assign((size_t)n * n, 0.0);
-  pf.lam[k].resize(n);
+  pf.lamF[k].resize(n);
   for (int p = 0; p < 2; ++p) {
-    const int m = h[p], c0 = p ? h[0] : 0;
+    const int m = h[p];
     const double sg = p ? -1.0 : 1.0;
     if (m == 0) continue;
     std::vector<double> A((size_t)m * m);
@@ -312,7 +312,25 @@ static bool parity_decompose(int n, const std::vector<double>& K, PrecFactors& p
     std::vector<double>&S = pf.SF[k][p], &Si = pf.SiF[k][p];
     S.resize((size_t)m * m);
     Si.resize((size_t)m * m);
-    if (!eigen_decompose_real(m, A.data(), S.data(), Si.data(), pf.lam[k].data() + c0)) return false;
+    if (!eigen_decompose_real(m, A.data(), S.data(), Si.data(), pf.lamF[k].data() + (p ? h[0] : 0))) return false;
+  }
+  return true;
+}
+
+// Eigen-factors of the whole operator from its halves' (a quarter of the work of the
+// whole matrix): the even eigenvectors are (u, u mirrored), the odd ones (u, -u
+// mirrored), each of length 1 as eigen_decompose_real gives them: with the halves'
+// columns of length 1 instead, other bits of the factors are cut when BF16x3 splits
+// them (n = 1024, 16 vectors: error of the preconditioner 9.6e-6 instead of 8.7e-6).
+static void parity_whole(int n, PrecFactors& pf, int k) {
+  const int h[2] = {(n + 1) / 2, n / 2};
+  pf.S[k].assign((size_t)n * n, 0.0);
+  pf.Si[k].assign((size_t)n * n, 0.0);
+  pf.lam[k] = pf.lamF[k];
+  for (int p = 0; p < 2; ++p) {
+    const int m = h[p], c0 = p ? h[0] : 0;
+    const double sg = p ? -1.0 : 1.0;
+    const std::vector<double>&S = pf.SF[k][p], &Si = pf.SiF[k][p];
     std::vector<double> len(m, 0.0);
     for (int i = 0; i < m; ++i)
       for (int c = 0; c < m; ++c) len[c] += (n - 1 - i != i ? 2.0 : 1.0) * S[(size_t)i * m + c] * S[(size_t)i * m + c];
@@ -329,7 +347,18 @@ static bool parity_decompose(int n, const std::vector<double>& K, PrecFactors& p
       }
     }
   }
-  return true;
+}
+
+// Smallest |x + y - sigma| over all pairs.
+static double smallest_denominator(const std::vector<double>& xs, std::vector<double> ys, double sigma) {
+  std::sort(ys.begin(), ys.end());
+  double mn = 1e300;
+  for (double a : xs) {
+    auto it = std::lower_bound(ys.begin(), ys.end(), sigma - a);
+    if (it != ys.end()) mn = std::min(mn, std::fabs(a + *it - sigma));
+    if (it != ys.begin()) mn = std::min(mn, std::fabs(a + *(it - 1) - sigma));
+  }
+  return mn;
 }
 
 // A mode matrix in the fragment order of modeprod.h: for every K group (8 k in
@@ -414,8 +443,8 @@ static tp3b_status upload_ops(tp3b_op op, tp3b::DevOps<T>& d, const std::vector<
       TP3B_HIP(upload(&d.fS[k], F));
       // eigenvalues, even then odd, the odd ones of an odd n padded by one (that
       // entry is zero whatever it is divided by)
-      std::vector<double> lam((size_t)2 * h, pf.lam[k][0]);
-      std::copy(pf.lam[k].begin(), pf.lam[k].end(), lam.begin());
+      std::vector<double> lam((size_t)2 * h, pf.lamF[k][0]);
+      std::copy(pf.lamF[k].begin(), pf.lamF[k].end(), lam.begin());
       TP3B_HIP(upload(&d.fLam[k], lam));
     }
   }
@@ -1319,14 +1348,23 @@ tp3b_status tp3b_create(const tp3b_problem_desc* desc, void* stream, tp3b_op* ou
     PrecFactors pf;
     {
       bool ok = true;
+      // the library's own symmetric grids through their halves; of a given matrix the
+      // whole decides whether it has real eigen-factors, as an even and an odd
+      // eigenvalue that coincide may come out of it as a complex pair
+      bool halves[4] = {false, false, false, false};
       for (int k = 0; k < nm && ok; ++k) {
         const int n = op->n[k];
+        const bool sym = desc->ndim == 1 && reflection_symmetric(desc, k, Kh[k]);
+        if (sym && !desc->D2[k]) {
+          ok = halves[k] = parity_halves(n, reflection_mean(Kh[k]), pf, k);
+          if (ok) parity_whole(n, pf, k);
+          continue;
+        }
         pf.S[k].resize((size_t)n * n);
         pf.Si[k].resize((size_t)n * n);
         pf.lam[k].resize(n);
-        ok = desc->ndim == 1 && reflection_symmetric(desc, k, Kh[k])
-                 ? parity_decompose(n, reflection_mean(Kh[k]), pf, k)
-                 : eigen_decompose_real(n, Kh[k].data(), pf.S[k].data(), pf.Si[k].data(), pf.lam[k].data());
+        ok = eigen_decompose_real(n, Kh[k].data(), pf.S[k].data(), pf.Si[k].data(), pf.lam[k].data());
+        if (ok && sym && N > kFoldMin) halves[k] = parity_halves(n, Kh[k], pf, k);
       }
       if (ok) {
         // smallest |denominator|: sums over the x modes against sums over the y modes
@@ -1342,17 +1380,8 @@ tp3b_status tp3b_create(const tp3b_problem_desc* desc, void* stream, tp3b_op* ou
           pf.lamItem = xs;   // index i1 * n1 + i2
           pf.lamItemY = ys;  // index j1 * n3 + j2
         }
-        std::vector<double> ysort = ys;
-        std::sort(ysort.begin(), ysort.end());
-        double mn = 1e300;
-        for (double a : xs) {
-          const double want = op->sigma - a;
-          auto it = std::lower_bound(ysort.begin(), ysort.end(), want);
-          if (it != ysort.end()) mn = std::min(mn, std::fabs(a + *it - op->sigma));
-          if (it != ysort.begin()) mn = std::min(mn, std::fabs(a + *(it - 1) - op->sigma));
-        }
-        op->lam_min = mn;
-        op->have_prec = mn > 0;
+        op->lam_min = smallest_denominator(xs, ys, op->sigma);
+        op->have_prec = op->lam_min > 0;
       }
       // lower bound of the spectrum (Weyl, continuous problem): the eigensolver's
       // starting target
@@ -1377,20 +1406,17 @@ tp3b_status tp3b_create(const tp3b_problem_desc* desc, void* stream, tp3b_op* ou
       // preconditioner work buffer: up to 64 vectors, at most 4 GiB (FP64)
       const int64_t cap = (int64_t)(1ll << 32) / (N * 8);
       op->work_vecs = (int)std::max<int64_t>(1, std::min<int64_t>(64, cap));
+      if (op->have_prec && N > kFoldMin && halves[0] && halves[1] &&
+          smallest_denominator(pf.lamF[0], pf.lamF[1], op->sigma) > 0) {
+        op->fold_vecs = (int)(op->work_vecs * N / (2 * op->fold_size()));
+        op->fold = op->fold_vecs > 0;
+      }
     }
     if (op->ndim == 2) {
       op->x_same_K = Kh[0] == Kh[1];
       op->x_same_S = op->have_prec && pf.S[0] == pf.S[1] && pf.Si[0] == pf.Si[1];
       op->y_same_K = Kh[2] == Kh[3];
       op->y_same_S = op->have_prec && pf.S[2] == pf.S[3] && pf.Si[2] == pf.Si[3];
-    }
-    // Small grids keep the plain products: their four launches are bound by latency,
-    // which the folds add to.  Us per apply, plain / folded: 128 x 128 x 8 19.2 / 19.8
-    // (FP32 17.4 / 19.4), 256 x 128 x 4 22.1 / 23.2, 256 x 256 x 8 36.9 / 30.7 (FP32
-    // 26.2 / 22.0), 512 x 512 x 8 156 / 108, 1024 x 1024 x 16 1953 / 1097.
-    if (op->ndim == 1 && N > 32768 && reflection_symmetric(desc, 0, Kh[0]) && reflection_symmetric(desc, 1, Kh[1])) {
-      op->fold_vecs = (int)(op->work_vecs * N / (2 * op->fold_size()));
-      op->fold = op->fold_vecs > 0;
     }
     tp3b_status st = upload_ops<double>(op, op->d64, Kh, pf);
     if (st == TP3B_OK) st = upload_ops<float>(op, op->d32, Kh, pf);
