@@ -346,7 +346,9 @@ tp3b_status tp3b_set_tile(tp3b_op op, int32_t tile);
  * preconditioner of this operator at `nvec` vectors in precision `prec` on
  * scratch blocks (HIP events, `reps` repetitions each) and keeps the fastest
  * per (precision, apply kind).  Synchronous; allocates and frees its scratch
- * blocks.  best_ms (optional, host 2 doubles) receives the winning times. */
+ * blocks.  best_ms (optional, host 2 doubles) receives the winning times.  A
+ * preconditioner that runs as one launch (modes up to 48, in FP32 up to 64) has no
+ * tile to choose: its time is that of the launch. */
 tp3b_status tp3b_autotune(tp3b_op op, int32_t prec, int32_t nvec, int32_t reps, double* best_ms);
 
 /* Library-internal dense host routine exposed for host-side testing: real Schur

@@ -1573,6 +1573,8 @@ tp3b_status tp3b_autotune_batched(const tp3b_op* ops, int32_t count, int32_t pre
           bool all = true;
           for (int i : gi) all &= ops[i]->have_prec;
           if (!all) break;
+          // no tile to choose where the preconditioner is one launch
+          if (f64 ? prec_one<double>(ops[gi[0]], bf3, -1) : prec_one<float>(ops[gi[0]], bf3, -1)) break;
         }
         double best = 1e300;
         int best_tile = -1;

@@ -179,13 +179,17 @@ template <typename T>
 ModeProd<T> h_job(tp3b_op op, int nvec, const T* X, int64_t ldx, T* Y, int64_t ldy, const double* shifts);
 template <typename T>
 ModeProd<T> prec_job(tp3b_op op, int st, int nv, const T* X, int64_t ldx, T* Y, int64_t ldy, bool fold);
-// Whether the preconditioner runs folded (FP64 and FP32).
 // Whether a 1D preconditioner apply runs as one launch (small grids, unless a tile
 // is asked for), and its job.
 template <typename T>
-bool prec_one(tp3b_op op, bool bf3);
+bool prec_one(tp3b_op op, bool bf3, int tile_override);
+template <typename T>
+bool prec_one(tp3b_op op, bool bf3) {
+  return prec_one<T>(op, bf3, op->tile_override);
+}
 template <typename T>
 tp3b::Prec1D<T> prec1d_job(tp3b_op op, int nvec, const T* X, int64_t ldx, T* Y, int64_t ldy);
+// Whether the preconditioner runs folded (FP64 and FP32).
 bool prec_folded(tp3b_op op, bool bf3);
 int choose_tile(int M, int Nc, int64_t nbatch, bool bf3);
 // Second-derivative matrix (row-major, desc->D2[k] when given) and ascending

@@ -631,8 +631,8 @@ ModeProd<T> prec_job(tp3b_op op, int st, int nv, const T* X, int64_t ldx, T* Y, 
   return a;
 }
 template <typename T>
-bool prec_one(tp3b_op op, bool bf3) {
-  return op->ndim == 1 && dev_ops<T>(op).frSi[0] && !bf3 && op->tile_override < 0;
+bool prec_one(tp3b_op op, bool bf3, int tile_override) {
+  return op->ndim == 1 && dev_ops<T>(op).frSi[0] && !bf3 && tile_override < 0;
 }
 
 template <typename T>
@@ -650,7 +650,7 @@ tp3b::Prec1D<T> prec1d_job(tp3b_op op, int nvec, const T* X, int64_t ldx, T* Y, 
   return a;
 }
 #define TP3B_JOBS(T)                                                                                  \
-  template bool prec_one<T>(tp3b_op, bool);                                                           \
+  template bool prec_one<T>(tp3b_op, bool, int);                                                      \
   template tp3b::Prec1D<T> prec1d_job<T>(tp3b_op, int, const T*, int64_t, T*, int64_t);               \
   template ModeProd<T> h_job<T>(tp3b_op, int, const T*, int64_t, T*, int64_t, const double*);          \
   template ModeProd<T> prec_job<T>(tp3b_op, int, int, const T*, int64_t, T*, int64_t, bool);
@@ -1178,8 +1178,11 @@ static tp3b_status autotune_impl(tp3b_op op, int nvec, int reps, double* best_ms
     // overflow in the preconditioner's divide.
     (void)hipMemset(X, 0, sizeof(T) * op->N * nvec);
     const int saved = op->tile_override;
-    for (int tile = 0; tile < NUM_TILE_CFGS; ++tile) {
-      const int tm = tile_rows(tile), tn = tile_cols(tile);
+    // a preconditioner of one launch has no tile: that launch is timed (-1), and no
+    // tile is kept
+    const bool one = kind == 1 && prec_one<T>(op, bf3, -1);
+    for (int tile = one ? -1 : 0; tile < (one ? 0 : (int)NUM_TILE_CFGS); ++tile) {
+      const int tm = one ? 0 : tile_rows(tile), tn = one ? 0 : tile_cols(tile);
       if (tm > 32 && (tm > op->n[op->ndim == 1 ? 0 : 2] || tn > op->n[op->ndim == 1 ? 1 : 3])) continue;
       if (bf3 && tm == 32) continue;  // the smallest BF16x3 tile is 64 x 64
       op->tile_override = tile;
