@@ -5,10 +5,24 @@
 // Included by HIP translation units only.
 #pragma once
 
+#include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
 #include "kernels.h"
+
+// Launch with the timing events of launch_timing() when it is set.
+#define TP3B_MP_LAUNCH(KERN, GRID, BLOCK, S, ARG)                                                 \
+  do {                                                                                     \
+    LaunchTiming* lt_ = launch_timing();                                                   \
+    if (lt_) {                                                                             \
+      hipEvent_t st_ = lt_->started ? nullptr : lt_->start;                                \
+      lt_->started = true;                                                                 \
+      hipExtLaunchKernelGGL(KERN, dim3(GRID), dim3(BLOCK), 0, S, st_, lt_->stop, 0, ARG);  \
+    } else {                                                                               \
+      hipLaunchKernelGGL(KERN, dim3(GRID), dim3(BLOCK), 0, S, ARG);                        \
+    }                                                                                      \
+  } while (0)
 
 namespace tp3b {
 

@@ -59,7 +59,7 @@ std::vector<double> colmajor(const std::vector<double>& A, int ld, int r0, int c
 // timestamp events (LaunchTiming): kind 0 = FP64 Hamiltonian applies, 1 =
 // low-precision Hamiltonian applies, 2 = FP64 preconditioner applies, 3 =
 // low-precision preconditioner applies.  Launches inside a captured graph are
-// not timed (paused).
+// not timed (paused), nor are the 2D plane passes.
 struct KernelTimer {
   bool on = false, paused = false;
   std::vector<hipEvent_t> ev;  // pairs (2i, 2i+1) bracket one launch group
@@ -86,7 +86,9 @@ struct KernelTimer {
     return hipSuccess;
   }
   void end() {
-    if (launch_timing() == &lt) launch_timing() = nullptr;
+    if (launch_timing() != &lt) return;
+    launch_timing() = nullptr;
+    if (!lt.started) used -= 2;  // no launch of the group takes the events
   }
   void collect(double* t, int64_t* n, int64_t* v) {
     for (size_t i = 0; i + 1 < used; i += 2) {

@@ -13,7 +13,6 @@
 // deterministic (no atomics).
 #include "kernels.h"
 
-#include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -29,19 +28,6 @@ LaunchTiming*& launch_timing() {
   static thread_local LaunchTiming* t = nullptr;
   return t;
 }
-
-// Launch with the timing events of launch_timing() when it is set.
-#define TP3B_MP_LAUNCH(KERN, GRID, BLOCK, S, ARG)                                                 \
-  do {                                                                                     \
-    LaunchTiming* lt_ = launch_timing();                                                   \
-    if (lt_) {                                                                             \
-      hipEvent_t st_ = lt_->started ? nullptr : lt_->start;                                \
-      lt_->started = true;                                                                 \
-      hipExtLaunchKernelGGL(KERN, dim3(GRID), dim3(BLOCK), 0, S, st_, lt_->stop, 0, ARG);  \
-    } else {                                                                               \
-      hipLaunchKernelGGL(KERN, dim3(GRID), dim3(BLOCK), 0, S, ARG);                        \
-    }                                                                                      \
-  } while (0)
 
 // ROLE only separates the kernel names seen by profilers: 0 = Hamiltonian apply
 // (both modes + potential), 1 = preconditioner mode products, 2 = 2D x-mode

@@ -1390,11 +1390,16 @@ hipError_t launch_prec1d(const Prec1D<T>& a, hipStream_t s) {
   if (a.nvec <= 0) return hipSuccess;
   const int n = a.M > a.Nc ? a.M : a.Nc;
   if (a.M < 1 || a.Nc < 1 || n > p1_small<T>()) return hipErrorInvalidValue;
-  const dim3 g(a.nvec);
-  if (n <= 16) hipLaunchKernelGGL((k_prec1d<T, 1>), g, dim3(64), 0, s, a);
-  else if (n <= 32) hipLaunchKernelGGL((k_prec1d<T, 2>), g, dim3(256), 0, s, a);
-  else if (n <= 48) hipLaunchKernelGGL((k_prec1d<T, 3>), g, dim3(576), 0, s, a);
-  else if constexpr (p1_small<T>() > 48) hipLaunchKernelGGL((k_prec1d<T, 4>), g, dim3(1024), 0, s, a);
+  const unsigned g = a.nvec;
+  if (n <= 16) {
+    TP3B_MP_LAUNCH((k_prec1d<T, 1>), g, 64, s, a);
+  } else if (n <= 32) {
+    TP3B_MP_LAUNCH((k_prec1d<T, 2>), g, 256, s, a);
+  } else if (n <= 48) {
+    TP3B_MP_LAUNCH((k_prec1d<T, 3>), g, 576, s, a);
+  } else if constexpr (p1_small<T>() > 48) {
+    TP3B_MP_LAUNCH((k_prec1d<T, 4>), g, 1024, s, a);
+  }
   return hipGetLastError();
 }
 
