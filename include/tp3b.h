@@ -137,8 +137,9 @@ tp3b_status tp3b_apply_H_shifted(tp3b_op op, int32_t prec, int32_t nvec, const v
 /* Y = (K - sigma I)^{-1} X with K the kinetic Kronecker sum (eq. (14)).  1D:
  * per vector the Sylvester equation (K_x - s_x I) Z + Z (K_y - s_y I)^T = B,
  * s_x + s_y = sigma, split in proportion to c_x and c_y, solved in the
- * eigenbasis of K_x and K_y (four mode products and a pointwise divide), which
- * is exact, as the paper's Bartels-Stewart solve is.  2D (the paper has no 2D
+ * eigenbasis of K_x and K_y (four mode products and a pointwise divide; one launch
+ * on grids of up to 48 points per mode, in FP32 up to 64), which is exact, as the
+ * paper's Bartels-Stewart solve is.  2D (the paper has no 2D
  * preconditioner; this extends the same construction): the four-mode sum
  * K_x1 + K_x2 + K_y1 + K_y2 - sigma is inverted in the eigenbases of the four
  * mode operators (eight mode products and a divide).  TP3B_ENOTSUP if a mode
@@ -303,7 +304,9 @@ tp3b_status tp3b_apply_H_batched(const tp3b_op* ops, int32_t count, int32_t prec
                                  const int64_t* ldy, const double* const* shifts, void* stream);
 
 /* Y_i = (K_i - sigma_i I)^{-1} X_i for i < count (tp3b_apply_prec per
- * instance, four grouped mode-product launches).  nvec <= 64. */
+ * instance: the small grids in one grouped launch, the others in four steps, each a
+ * grouped launch for the plain and for the folded products of every tile shape in
+ * use).  nvec <= 64. */
 tp3b_status tp3b_apply_prec_batched(const tp3b_op* ops, int32_t count, int32_t prec, int32_t nvec,
                                     const void* const* X, const int64_t* ldx, void* const* Y,
                                     const int64_t* ldy, void* stream);

@@ -40,8 +40,8 @@ struct ModeProd {
   // NULL: the operand is split while it is staged.
   const unsigned short* Lhl;
   const unsigned short* Rhl;
-  // FP64 and FP32 products (modeprod.h): L and R in fragment order
-  // (mp_fragments), used instead of the two above.
+  // FP64 and FP32 products (modeprod.h): the two operators in fragment order
+  // (mp_fragments), used instead of L and R.
   const T* LF;
   const T* RF;
   // Folded products (mode other than MP_PLAIN): the even factor at LF or RF, the
@@ -99,8 +99,8 @@ inline int tile_cols(int tile) {
   return (tile == TILE_32 || tile == TILE_32W8) ? 32 : ((tile == TILE_64) ? 64 : 128);
 }
 
-// Optional kernel timestamps for the mode-product launches of the calling
-// thread.  While launch_timing() points at a LaunchTiming, the first launch
+// Optional kernel timestamps for the mode-product launches (and the one-launch
+// preconditioner) of the calling thread.  While launch_timing() points at a LaunchTiming, the first launch
 // records `start` when it begins and every launch records `stop` when it ends,
 // so the pair spans the launch group without any dispatch gap before it.
 // Launches that are being captured into a graph must not be timed.
@@ -251,8 +251,6 @@ hipError_t launch_convert(int64_t N, int ncol, double alpha, const TI* X, int64_
 // Cholesky-QR pair passes the first one's flags).  One wavefront.
 hipError_t launch_chol_small(int nx, const double* G, const double* norm0sq, double drop_tol,
                              double* R, int* flags, hipStream_t s, const int* skip = nullptr);
-// n0[j] = G[j + j nx] for j < nx (the diagonal of a Gram matrix); flag[0] = 1 if
-// any of them is not finite, 0 otherwise.  Single thread.
 // Long blocks (the fits rules): C = Q^T X (nq x nx) and Gram = X^T X (nx x nx) in one
 // pass; the Gram matrix of X R^{-1}, X as it is; X <- (X R^{-1}) R2^{-1}.
 // `partial` as for launch_dot_tn of the larger of the two dots (the Gram).
@@ -264,6 +262,8 @@ hipError_t launch_trsm_gram(int64_t N, int nx, const double* R, const double* X,
                             double* partial, hipStream_t s);
 hipError_t launch_trsm_two(int64_t N, int nx, const double* R, const double* R2, double* X, int64_t ldx,
                            hipStream_t s);
+// n0[j] = G[j + j nx] for j < nx (the diagonal of a Gram matrix); flag[0] = 1 if
+// any of them is not finite, 0 otherwise.  Single thread.
 hipError_t launch_gram_diag(int nx, const double* G, double* n0, int* flag, hipStream_t s);
 // X (N x nx) <- X R^{-1} for upper-triangular R (column-major nx x nx).
 hipError_t launch_trsm_right(int64_t N, int nx, const double* R, double* X, int64_t ldx,

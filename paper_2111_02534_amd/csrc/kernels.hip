@@ -603,8 +603,8 @@ static bool launch_dot_long(int64_t N, int p, int q, const TA* A, int64_t lda, c
 // A Gram-Schmidt update fused with the dot that follows it (long blocks,
 // FP64): per row, Xout = Xin - Q C (nq x nx, nx <= 16, Q C on the matrix
 // cores), then the partials of the next dot on the updated rows, Q^T Xout
-// (SELF false: the second Gram-Schmidt pass; the same steps, workgroups and
-// product order as k_dot_lds, so it equals launch_dot_tn on the stored Xout)
+// (SELF false: the second Gram-Schmidt pass; the steps and product order of
+// k_dot_lds, but the grid is its own, so the partial sums may be cut elsewhere)
 // or Xout^T Xout (SELF true: the Gram matrix of the Cholesky-QR).  Rows are
 // staged through LDS in steps as in k_dot_lds.  Xin may equal Xout
 // (each row is read before it is written, by the same workgroup).  Bound by
