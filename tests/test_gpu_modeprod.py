@@ -3,8 +3,8 @@ at and one past the MFMA blocks, the tiles and the K chunks, odd sizes (the
 middle entry of a folded mode is its own mirror; rows that are no whole number
 of 16-byte pieces), leading dimensions that misalign every second vector, and
 single vectors.  Every size runs the Hamiltonian apply (plain products) and the
-preconditioner (folded products on these grids; plain ones on a parity half
-grid), in FP64 and FP32.
+preconditioner (one launch on the smallest, folded products above 32,768 points,
+plain products between and on a parity half grid), in FP64 and FP32.
 
 Bars: H within n-term rounding of NumPy's FP64 products with the same matrices,
 componentwise 4 (n_x + n_y + 1) units of |H||W| on N(0,1) blocks; the preconditioner within the

@@ -1,6 +1,6 @@
-"""The two-mode preconditioner on grids of up to 64 x 64 points, which runs as one
-launch: at the edges of the 16 x 16 MFMA blocks, with unequal modes, strided
-blocks and one more size than the rule takes.  Bars as for the other
+"""The two-mode preconditioner on grids of up to 48 x 48 (FP32: 64 x 64) points, which
+runs as one launch: at the edges of the 16 x 16 MFMA blocks, with unequal modes, strided
+blocks and sizes past the rule.  Bars as for the other
 preconditioner kernels against the oracle's Bartels-Stewart solve: FP64 1e-10,
 FP32 2e-5 (normwise)."""
 import numpy as np
