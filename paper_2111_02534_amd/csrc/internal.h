@@ -122,7 +122,7 @@ struct tp3b_op_s {
   int fold_vecs = 0;
   int64_t fold_size() const { return 4 * (int64_t)tp3b::fold_half(n[0]) * tp3b::fold_row(n[1]); }
   // vectors per group when nv vectors go through folded (groups of nearly equal size)
-  int fold_groups(int nv) const { return (nv + fold_vecs - 1) / fold_vecs; }
+  int fold_groups(int nv) const { return std::max(1, (nv + fold_vecs - 1) / fold_vecs); }
   int fold_step(int nv) const { return (nv + fold_groups(nv) - 1) / fold_groups(nv); }
   bool plane2d = false;         // 2D with every mode size <= P2_MAXN: two-pass applies
   bool x_same_K = false;        // 2D: the two x modes have the same operator K (and
